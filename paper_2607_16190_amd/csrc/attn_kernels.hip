@@ -943,12 +943,16 @@ __device__ __forceinline__ int pair_role(const BlockMap* __restrict__ table, con
   return poff > 0 ? 1 : 2;
 }
 
-__device__ __forceinline__ int xcc_id() {
-  uint32_t xcc;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-  return (int)(xcc & 0xfu);
-}
-
+// Each workgroup's first item is given by its index: workgroup b takes entry
+// b / kQueues of queue b % kQueues (workgroup n runs on XCD n % 8), so the
+// first G / kQueues entries of a queue (G workgroups) need no counter, and the
+// workgroups beyond the number of items leave at once. Later items are popped
+// with one atomic from the own queue; once that is empty, the eight counters
+// are read together and only queues that still hold items are popped from.
+// The counters lie in one cache line that every XCD's atomics meet in memory:
+// with every resident workgroup trying all eight queues (4096 atomics for the
+// 24 items of two heads of a 3x16x16 clip) they held up the working
+// workgroups' tile copies for most of the launch: 64 us, 28 us this way.
 template <bool F8>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnParams P, const int32_t* __restrict__ items,
                                                                           const int32_t* __restrict__ qbase,
@@ -956,7 +960,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
   __shared__ __align__(16) unsigned char ks_tile[kTileBytes];
   __shared__ __align__(16) unsigned char vs_tile[F8 ? kV8TileBytes : kTileBytes];
   __shared__ int next_slot, next_q;
-  int q = xcc_id() % kQueues;
+  const int groups = min((int)gridDim.x, qbase[kQueues]);
+  if ((int)blockIdx.x >= groups) return;
+  int q = blockIdx.x % kQueues;
+  // items of queue x that the workgroups' indices give away
+  auto given = [&](int x) { return (groups - x + kQueues - 1) / kQueues; };
+  bool first = true;
   // The trace record of an item is written at the top of the next iteration,
   // by thread 0 together with the queue pop: the loop then holds a single
   // region that only thread 0 runs, so the compiler keeps every lane of
@@ -967,19 +976,36 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
     if (threadIdx.x == 0) {
       if (prec >= 0) trace_record(P, prec, ppoff, pt0, pt1, pcyc);
       int slot = -1, qq = q;
-      for (int t = 0; t < kQueues; ++t) {
-        qq = (q + t) % kQueues;
-        const int len = qbase[qq + 1] - qbase[qq];
-        if (len <= 0) continue;
-        const int k = atomicAdd(&qctr[qq], 1);
-        if (k < len) {
-          slot = qbase[qq] + k;
-          break;
+      const int b0 = qbase[q], len = qbase[q + 1] - b0, own = given(q);
+      if (first && (int)(blockIdx.x / kQueues) < len) {
+        slot = b0 + (int)(blockIdx.x / kQueues);
+      } else if (len > own) {
+        const int k = own + atomicAdd(&qctr[q], 1);
+        slot = k < len ? b0 + k : -1;
+      }
+      if (slot < 0) {
+        int ctr[kQueues];
+#pragma unroll
+        for (int x = 0; x < kQueues; ++x)
+          ctr[x] = __hip_atomic_load(&qctr[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned left = 0;
+#pragma unroll
+        for (int x = 0; x < kQueues; ++x)
+          left |= given(x) + ctr[x] < qbase[x + 1] - qbase[x] ? 1u << x : 0u;
+        for (int t = 1; t < kQueues && slot < 0; ++t) {
+          const int x = (q + t) % kQueues;
+          if (!((left >> x) & 1u)) continue;
+          const int k = given(x) + atomicAdd(&qctr[x], 1);
+          if (k < qbase[x + 1] - qbase[x]) {
+            slot = qbase[x] + k;
+            qq = x;
+          }
         }
       }
       next_slot = slot;
       next_q = qq;
     }
+    first = false;
     __syncthreads();
     const int slot = __builtin_amdgcn_readfirstlane(next_slot);
     q = __builtin_amdgcn_readfirstlane(next_q);  // keep stealing from a queue that had work
