@@ -737,8 +737,8 @@ def main():
             "unit": "TFLOP/s",
             "frac": round(useful_flops / t_attn / 1e12 / peak, 4),
             "traffic": traffic,
-            "kernel": "attn_persistent_kernel (fva_attn; timed with its plan_kernel)" if not fp8 else
-            "attn_persistent_kernel<true> (fva_attn_fp8v; timed with its plan_kernel); peak = bf16 Q K^T and "
+            "kernel": "attn_persistent_kernel (fva_attn; timed with its prep_kernel)" if not fp8 else
+            "attn_persistent_kernel<true> (fva_attn_fp8v; timed with its prep_kernel); peak = bf16 Q K^T and "
             "fp8 P V at their own peaks",
             "algorithmic_flops_per_launch": useful_flops,
             "attn_source_digest": digest,

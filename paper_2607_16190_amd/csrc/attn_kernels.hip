@@ -14,7 +14,7 @@
 // product (8 consecutive keys per lane) without any register shuffle.
 //
 // Scheduling: a persistent grid (2 workgroups per CU) pulls items from one
-// queue per XCD. plan_kernel cuts every head's query blocks into 8 runs of
+// queue per XCD. prep_kernel cuts every head's query blocks into 8 runs of
 // equal kept-block cost, run x into queue x, heads in decreasing cost, so the
 // XCDs stay balanced by construction, work on the same head together (its K/V
 // stay in the shared last-level cache) and the workgroups resident on one XCD
@@ -104,7 +104,7 @@ __device__ __forceinline__ int key_of_row(int rho) {
 }
 
 // Uniform per-block constants for mapping a packed row index to its token,
-// one 32-byte record per block in the attention workspace (block_table_kernel
+// one 32-byte record per block in the attention workspace (number_blocks
 // fills it once per launch, so the block loop does no integer division).
 struct BlockMap {
   int tbase;      // token of the box origin
@@ -125,7 +125,7 @@ __device__ __forceinline__ BlockMap block_map(const Geometry& g, int j) {
   m.mp = (65536 + m.plane - 1) / m.plane;
   m.mx = (65536 + m.ex - 1) / m.ex;
   m.n = b.n;
-  m.pslot = -1;  // numbered by block_table_kernel
+  m.pslot = -1;  // numbered by number_blocks
   m.poff = pair_partner(g, j);
   return m;
 }
@@ -1051,10 +1051,90 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
   }
 }
 
-constexpr int kMinChunk = 32;      // smallest automatic chunk (kept blocks)
-constexpr int kPlanLdsHeads = 1024;  // heads whose queue bookkeeping the plan keeps in LDS
+constexpr int kMinChunk = 32;        // smallest automatic chunk (kept blocks)
+constexpr int kPlanThreads = 1024;   // one thread per block of the tiling
+constexpr int kPlanLdsHeads = 1024;  // heads whose bookkeeping the plan keeps in LDS
+static_assert(kMaxBlocks <= kPlanThreads, "one thread per block");
 
-// Builds the work list (one workgroup of 1024 threads).
+// Block records of the tiling, one thread per block of one workgroup, with the
+// query-block pairs numbered in the order of their first block: returns thread
+// j's record (block j) and leaves the first block of every pair in pfirst.
+__device__ __forceinline__ BlockMap number_blocks(const Geometry& g, int* wsum, int* pfirst) {
+  const int j = threadIdx.x;
+  const int lane = j & 63;
+  const int wave = j >> 6;
+  BlockMap m = {};
+  int first = 0;
+  if (j < g.nb) {
+    m = block_map(g, j);
+    first = m.poff > 0 ? 1 : 0;
+  }
+  const int incl = wave_incl_scan_i32(first, lane);
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int before = incl - first;
+  for (int w = 0; w < wave; ++w) before += wsum[w];
+  m.pslot = first ? before : -1;
+  if (first) pfirst[before] = j;
+  __syncthreads();
+  return m;
+}
+
+// Union list of one query-block pair (rows r, r2) by one wave: the two rows'
+// kept sets become bitmaps in LDS, read back in ascending block order as
+// entries j | (j not kept by the first row) << 16 | (j not kept by the second
+// row) << 17. An entry repeated in a kept list counts once.
+constexpr int kPairWords = kMaxBlocks / 64;
+
+template <int R>
+__device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, const int32_t* __restrict__ kv_idx,
+                                          int r, int r2, int nb, unsigned long long* bw, int lane,
+                                          int32_t* __restrict__ out) {
+  // both lists whole, with every load in flight (entries past a row's count
+  // are loaded, in bounds, and left out)
+  int e[2][R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int a = min(64 * k + lane, nb - 1);
+    e[0][k] = kv_idx[(int64_t)r * nb + a];
+    e[1][k] = kv_idx[(int64_t)r2 * nb + a];
+  }
+  const int c[2] = {min(counts[r], nb), min(counts[r2], nb)};
+  if (lane < 2 * kPairWords) bw[lane] = 0ull;
+  wave_sync();
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int j = min(max(e[s][k], 0), nb - 1);
+      if (64 * k + lane < c[s]) atomicOr(&bw[s * kPairWords + (j >> 6)], 1ull << (j & 63));
+    }
+  }
+  wave_sync();
+  int n = 0;
+  for (int w = 0; w * 64 < nb; ++w) {
+    const int j = 64 * w + lane;
+    const int ka = (int)((bw[w] >> lane) & 1ull);
+    const int kb = (int)((bw[kPairWords + w] >> lane) & 1ull);
+    const bool keep = (ka | kb) != 0;  // bits past nb are never set
+    const uint64_t m = __ballot(keep);
+    if (keep) out[n + lanes_below(m)] = j | ((ka ^ 1) << 16) | ((kb ^ 1) << 17);
+    n += __popcll(m);
+  }
+  wave_sync();  // the bitmaps are cleared for the next pair only after every lane read them
+  return n;
+}
+
+// Everything the attention needs before its first item, in one launch.
+// Workgroup 0 builds the work list; the others derive the block records
+// (workgroup 1 writes them) and, if pairs > 0, build the pairs' union lists,
+// one wave per pair. The lists of all pairs are built, also of those that the
+// plan will not form because a row of theirs is split: so nothing here waits
+// for the plan. All of it is latency: loads that do not depend on one another
+// are issued together, and the plan's passes (four, with a barrier between)
+// exchange only per-head values, in LDS. As three launches, with the plan's
+// values in memory: 18 us for 2 heads of 12 blocks, 44 us for 5 of 308 and 71
+// us for 40 of 660; this way 6, 15 and 44 us.
 //
 // Chunks (the split part of the scheduler): with S = `forced` (> 0) or, by
 // default, S = max(kMinChunk, ceil(total / (2 * slots))), total being the sum
@@ -1066,9 +1146,9 @@ constexpr int kPlanLdsHeads = 1024;  // heads whose queue bookkeeping the plan k
 // (the sum of ceil(c / S) over rows with c > S is at most 2 * total / S). If
 // the chunks would exceed chunk_cap, no row is split.
 //
-// Pairs (pairing != 0): the final S goes to *psplit for the pair-list and
-// attention kernels; a pair's first row costs its larger kept count + 1 (the
-// union it runs is about that long) and its second row 1 (an empty item).
+// Pairs: the final S goes to *psplit for the attention kernel; a pair's first
+// row costs its larger kept count + 1 (the union it runs is about that long)
+// and its second row 1 (an empty item).
 //
 // Queues: heads are taken in decreasing order of cost. Each head's query
 // blocks are cut into kQueues contiguous runs of about equal cost, run x going
@@ -1077,335 +1157,259 @@ constexpr int kPlanLdsHeads = 1024;  // heads whose queue bookkeeping the plan k
 // and the resident workgroups of one XCD work on neighbouring query blocks
 // (their kept K/V blocks overlap in L2).
 //
-// Scratch: per head cost, rank, run starts [kQueues + 1], queue offsets
-// [kQueues]; per row the exclusive prefixes of chunks and split rows.
-__global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ counts, int n_heads, Geometry g,
-                                                   int slots, int forced, int chunk_cap, int32_t* __restrict__ items,
-                                                   int32_t* __restrict__ qbase, int32_t* __restrict__ qctr,
-                                                   int32_t* __restrict__ hscratch, int32_t* __restrict__ rscratch,
-                                                   int4* __restrict__ chunks, int4* __restrict__ splits,
-                                                   int32_t* __restrict__ n_split, const BlockMap* __restrict__ table,
-                                                   int pairing, int32_t* __restrict__ psplit) {
-  __shared__ long long wtot[16];
-  __shared__ int lds_order[kPlanLdsHeads];
-  __shared__ int lds_cost[kPlanLdsHeads];
-  __shared__ int lds_len[kPlanLdsHeads * kQueues];
+// Scratch: per head cost, rank, run starts [kQueues], items before each run
+// [kQueues + 1], first chunk and first split record; in LDS up to
+// kPlanLdsHeads heads, else in hscratch and (the last two) rscratch. R: rounds
+// of 64 rows per head (a lane keeps a row's count of every round in registers).
+template <bool IN_LDS, int R>
+__global__ __launch_bounds__(kPlanThreads) void prep_kernel(
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ kv_idx, int n_heads, Geometry g, int slots,
+    int forced, int chunk_cap, int32_t* __restrict__ items, int32_t* __restrict__ qbase, int32_t* __restrict__ qctr,
+    int32_t* hscratch, int32_t* rscratch, int4* __restrict__ chunks, int4* __restrict__ splits,
+    int32_t* __restrict__ n_split, BlockMap* __restrict__ table, int pairs_head, int32_t* __restrict__ psplit,
+    int32_t* __restrict__ plist, int32_t* __restrict__ pcount) {
+  constexpr int nwaves = kPlanThreads / 64;
+  __shared__ int lds_head[IN_LDS ? kPlanLdsHeads * (4 + 2 * kQueues + 1) : 1];
   __shared__ int poffs[kMaxBlocks];
+  __shared__ long long wtot[nwaves];
+  __shared__ int qlen[kQueues];
+  __shared__ unsigned long long bits[nwaves][2 * kPairWords];
   const int nb = g.nb;
-  const int rows = n_heads * nb;
-  const bool in_lds = n_heads <= kPlanLdsHeads;
-  int32_t* hcost = hscratch;
-  int32_t* horder = hcost + n_heads;
-  int32_t* hstart = horder + n_heads;                  // [n_heads][kQueues + 1]
-  int32_t* hoff = hstart + (size_t)n_heads * (kQueues + 1);  // [n_heads][kQueues]
-  int32_t* cpre = rscratch;                            // [rows + 1] chunks before row r
-  int32_t* spre = cpre + rows + 1;                     // [rows + 1] split rows before row r
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int nwaves = blockDim.x >> 6;
-  auto kept_of = [&](int r) {
-    const int c = counts[r];
-    return c < 0 ? 0 : (c > nb ? nb : c);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  if (blockIdx.x > 0) {
+    const BlockMap m = number_blocks(g, (int*)wtot, poffs);
+    if (blockIdx.x == 1 && (int)threadIdx.x < nb) table[threadIdx.x] = m;
+    const int n_pairs = n_heads * pairs_head;
+    for (int slot = (blockIdx.x - 1) * nwaves + wave; slot < n_pairs; slot += (gridDim.x - 1) * nwaves) {
+      const int bh = slot / pairs_head;
+      const int i = poffs[slot - bh * pairs_head];
+      const int r = bh * nb + i;
+      const int n = pair_union<R>(counts, kv_idx, r, r + pair_partner(g, i), nb, bits[wave], lane,
+                               plist + (int64_t)slot * nb);
+      if (lane == 0) pcount[slot] = n;
+    }
+    return;
+  }
+
+  int* hcost = IN_LDS ? lds_head : hscratch;
+  int* horder = hcost + n_heads;
+  int* hstart = horder + n_heads;                          // [n_heads][kQueues]
+  int* hitem = hstart + (int64_t)n_heads * kQueues;        // [n_heads][kQueues + 1]
+  int* hchunk = IN_LDS ? hitem + n_heads * (kQueues + 1) : rscratch;
+  int* hsplit = hchunk + n_heads;
+
+  // a lane's rows of head h: i = 64k + lane, all loads in flight at once
+  // (lanes past the head re-read its last row)
+  auto load_counts = [&](int h, int (&c)[R]) {
+    const int32_t* hc = counts + (int64_t)h * nb;
+#pragma unroll
+    for (int k = 0; k < R; ++k) c[k] = hc[min(64 * k + lane, nb - 1)];
+#pragma unroll
+    for (int k = 0; k < R; ++k) c[k] = min(max(c[k], 0), nb);
   };
 
-  // 0. chunk size. One workgroup does all of the plan, so its time is load
-  //    latency: every thread keeps eight loads in flight per step (lanes past
-  //    the last row re-read it), here and in the passes below.
+  // 0. chunk size from the total; pair partner offsets (> 0: first of a pair,
+  //    < 0: second, 0: none)
   long long tsum = 0;
-  for (int r0 = threadIdx.x; r0 < rows; r0 += 8 * (int)blockDim.x) {
-    int c8[8];
+  for (int h = wave; h < n_heads; h += nwaves) {
+    int c[R];
+    load_counts(h, c);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) c8[u] = counts[min((int64_t)r0 + (int64_t)u * blockDim.x, (int64_t)rows - 1)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c8[u] < 0 ? 0 : (c8[u] > nb ? nb : c8[u]);
-      tsum += (int64_t)r0 + (int64_t)u * blockDim.x < rows ? c + 1 : 0;
-    }
+    for (int k = 0; k < R; ++k) tsum += 64 * k + lane < nb ? c[k] + 1 : 0;
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) tsum += __shfl_xor(tsum, o);
+  if ((int)threadIdx.x < nb) poffs[threadIdx.x] = pairs_head ? pair_partner(g, threadIdx.x) : 0;
+  tsum = (long long)wave_sum_u64((uint64_t)tsum);
   if (lane == 0) wtot[wave] = tsum;
   __syncthreads();
   long long total = 0;
+#pragma unroll
   for (int w = 0; w < nwaves; ++w) total += wtot[w];
-  __syncthreads();  // wtot is reused below; every wave holds the same total
   int S = forced > 0 ? forced : (int)max((long long)kMinChunk, (total + 2LL * slots - 1) / (2LL * slots));
 
-  // 1. items per row (1, or its chunks): when no row can exceed S (the usual
-  //    case with many rows per slot) item r is row r and nothing else is
-  //    built. Otherwise one pass over tiles of 1024 rows scans, packed in one
-  //    64-bit word, the chunks (low half) and split rows (high half) before
-  //    every row; the items before row r are r + chunks - split rows.
-  const bool may_split = S < nb;
-  if (may_split) {
-    for (int attempt = 0; attempt < 2; ++attempt) {
-      auto packed = [&](int r) -> uint64_t {
-        if (r >= rows) return 0ull;
-        const int c = kept_of(r);
-        return c > S ? ((uint64_t)1 << 32) | (uint64_t)((c + S - 1) / S) : 0ull;
-      };
-      uint64_t run = 0;  // over the tiles before this one
-      for (int base = 0; base < rows; base += 1024) {
-        const int r = base + (int)threadIdx.x;
-        const uint64_t v = packed(r);
-        const uint64_t incl = wave_incl_scan_u64(v, lane);
-        if (lane == 63) wtot[wave] = (long long)incl;
-        __syncthreads();
-        uint64_t before = run, all = run;
-        for (int w = 0; w < nwaves; ++w) {
-          const uint64_t t = (uint64_t)wtot[w];
-          before += w < wave ? t : 0ull;
-          all += t;
+  // 1. per head (one wave): cost, equal-cost runs, the items before each run,
+  //    chunks and split rows; a second time without splitting if the chunks
+  //    exceed the workspace's records
+  for (int attempt = 0;; ++attempt) {
+    for (int h = wave; h < n_heads; h += nwaves) {
+      int c[R], cn[R];
+      const int32_t* hc = counts + (int64_t)h * nb;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int i = min(64 * k + lane, nb - 1);
+        c[k] = hc[i];
+        cn[k] = hc[i + poffs[i]];  // the partner's count (an unpaired row's own)
+      }
+      int hsum = 0, spl = 0;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int own = min(max(c[k], 0), nb), p = min(max(cn[k], 0), nb);
+        const bool in = 64 * k + lane < nb;
+        const int poff = poffs[min(64 * k + lane, nb - 1)];
+        // cn becomes the row's cost, c its items
+        const int cost = poff == 0 || own > S || p > S ? own + 1 : poff > 0 ? max(own, p) + 1 : 1;
+        cn[k] = in ? cost : 0;
+        c[k] = !in ? 0 : own > S ? (own + S - 1) / S : 1;
+        spl += in && own > S ? 1 : 0;
+        hsum += cn[k];
+      }
+      const uint64_t sums = wave_sum_u64(((uint64_t)(uint32_t)hsum << 32) | (uint32_t)spl);
+      hsum = (int)(sums >> 32);
+      const int splits_h = (int)(uint32_t)sums;
+      // run of row i = floor(kQueues * (cost before row i) / hsum), a
+      // non-decreasing function of i; run x starts at the first row whose run
+      // is >= x (nb when there is none). It is >= x exactly when kQueues *
+      // before >= x * hsum: no division, and no overflow (before <= hsum <=
+      // nb * (nb + 1)). The row where runs begin writes their starts.
+      int* st = hstart + (int64_t)h * kQueues;
+      int* hi = hitem + (int64_t)h * (kQueues + 1);
+      int cost_before = 0, items_before = 0, run_last = -1;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int i = 64 * k + lane;
+        if (64 * k < nb) {  // (a guard, not a break: the loop stays unrolled and the costs in registers)
+          const int cincl = wave_incl_scan_i32(cn[k], lane);
+          const int nincl = wave_incl_scan_i32(c[k], lane);
+          const int before8 = kQueues * (cost_before + cincl - cn[k]);
+          int run = 0;
+#pragma unroll
+          for (int x = 1; x < kQueues; ++x) run += before8 >= x * hsum ? 1 : 0;
+          const int up = __shfl_up(run, 1);
+          const int prev = lane == 0 ? run_last : up;
+          if (i < nb) {
+            for (int x = prev + 1; x <= run; ++x) {
+              st[x] = i;
+              hi[x] = items_before + nincl - c[k];
+            }
+          }
+          run_last = __builtin_amdgcn_readlane(run, min(63, nb - 1 - 64 * k));
+          cost_before += __builtin_amdgcn_readlane(cincl, 63);
+          items_before += __builtin_amdgcn_readlane(nincl, 63);
         }
-        __syncthreads();
-        if (r < rows) {
-          const uint64_t ex = before + incl - v;
-          cpre[r] = (int)(uint32_t)ex;
-          spre[r] = (int)(ex >> 32);
-        }
-        run = all;
       }
-      if ((int)(uint32_t)run > chunk_cap && attempt == 0) {
-        S = 0x7fffffff;  // nothing is split
-        continue;
+      if (lane <= kQueues && lane > run_last) {  // runs without a row, and the end
+        if (lane < kQueues) st[lane] = nb;
+        hi[lane] = items_before;
       }
-      if (threadIdx.x == 0) {
-        cpre[rows] = (int)(uint32_t)run;
-        spre[rows] = (int)(run >> 32);
-        *n_split = (int)(run >> 32);
+      if (lane == 0) {
+        hcost[h] = hsum;
+        hchunk[h] = items_before - (nb - splits_h);
+        hsplit[h] = splits_h;
       }
-      break;
-    }
-  } else if (threadIdx.x == 0) {
-    *n_split = 0;
-  }
-  __syncthreads();
-  // items before row r (ipre[r])
-  auto ipre = [&](int r) { return may_split ? r + cpre[r] - spre[r] : r; };
-  if (pairing && threadIdx.x == 0) *psplit = S;
-  // Pair partner offset of every block (> 0: first of a pair, < 0: second,
-  // 0: none), from the block records once; the same rule as pair_role.
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) poffs[i] = pairing ? table[i].poff : 0;
-  __syncthreads();
-  // cost of a row from its partner offset, its kept count and its partner's
-  auto row_cost = [&](int poff, int c, int cn) {
-    if (poff == 0 || c > S || cn > S) return c + 1;  // not in a formed pair
-    return poff > 0 ? max(c, cn) + 1 : 1;
-  };
-  auto clamp_count = [&](int c) { return c < 0 ? 0 : (c > nb ? nb : c); };
-
-  // 2. head costs and equal-cost runs (one wave per head): every count the
-  //    head's costs need is loaded first (lanes past nb re-read the last
-  //    block's; an unpaired row reads its own count as its partner's); a
-  //    lane's costs stay in registers between the two passes
-  for (int h = wave; h < n_heads; h += nwaves) {
-    const int32_t* hc = counts + (size_t)h * nb;
-    int pf[kMaxBlocks / 64], ca[kMaxBlocks / 64], cb[kMaxBlocks / 64];
-#pragma unroll
-    for (int k = 0; k < kMaxBlocks / 64; ++k) pf[k] = poffs[min(64 * k + lane, nb - 1)];
-#pragma unroll
-    for (int k = 0; k < kMaxBlocks / 64; ++k) {
-      const int i = min(64 * k + lane, nb - 1);
-      ca[k] = hc[i];
-      cb[k] = hc[i + pf[k]];
-    }
-    int cst[kMaxBlocks / 64];
-    int hsum = 0;
-#pragma unroll
-    for (int k = 0; k < kMaxBlocks / 64; ++k) {
-      const int cost = row_cost(pf[k], clamp_count(ca[k]), clamp_count(cb[k]));
-      cst[k] = 64 * k + lane < nb ? cost : 0;
-      hsum += cst[k];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) hsum += __shfl_xor(hsum, o);
-    if (lane == 0) {
-      hcost[h] = hsum;
-      if (in_lds) lds_cost[h] = hsum;
-    }
-    // run of row i = floor(kQueues * (cost before row i) / hsum), a
-    // non-decreasing function of i; run x starts at the first row whose run
-    // is >= x (nb when there is none).
-    int stx[kQueues + 1];
-#pragma unroll
-    for (int x = 0; x <= kQueues; ++x) stx[x] = nb;
-    int run_before = 0;
-#pragma unroll
-    for (int k = 0; k < kMaxBlocks / 64; ++k) {
-      const int i0 = 64 * k;
-      if (i0 < nb) {  // (a guard, not a break: the loop stays unrolled and cst in registers)
-        const int i = i0 + lane;
-        const int c = cst[k];
-        const int incl = wave_incl_scan_i32(c, lane);
-        const int before = run_before + incl - c;
-        // run >= x exactly when kQueues * before >= x * hsum: no division,
-        // and no overflow (before <= hsum <= nb * (nb + 1))
-#pragma unroll
-        for (int x = 0; x < kQueues; ++x) {
-          const uint64_t hit = __ballot(i < nb && before * kQueues >= x * hsum);
-          if (stx[x] == nb && hit) stx[x] = i0 + __ffsll((unsigned long long)hit) - 1;
-        }
-        run_before += __shfl(incl, 63);
-      }
-    }
-    int32_t* st = hstart + (size_t)h * (kQueues + 1);
-    if (lane == 0) {
-#pragma unroll
-      for (int x = 0; x <= kQueues; ++x) st[x] = stx[x];
-    }
-  }
-  __syncthreads();
-
-  // 3. head order by decreasing cost (ties: lower head first), from the LDS
-  //    copy of the costs when it holds them
-  auto rank_by_cost = [&](const int32_t* costs, int h) {
-    const int ch = costs[h];
-    int rank = 0;
-    for (int k = 0; k < n_heads; ++k) {
-      const int ck = costs[k];
-      rank += (ck > ch || (ck == ch && k < h)) ? 1 : 0;
-    }
-    return rank;
-  };
-  for (int h = threadIdx.x; h < n_heads; h += blockDim.x)
-    horder[in_lds ? rank_by_cost(lds_cost, h) : rank_by_cost(hcost, h)] = h;
-  __syncthreads();
-
-  // 4. queue offsets (in items) of every (head, run) and queue bases: a
-  //    walk over the heads in cost order, from LDS copies of the order and
-  //    of the item count of every (head, run) when they fit
-  if (in_lds) {
-    for (int r = threadIdx.x; r < n_heads; r += blockDim.x) {
-      const int h = horder[r];
-      const int32_t* st = hstart + (size_t)h * (kQueues + 1);
-      int stx[kQueues + 1], ip[kQueues + 1];
-#pragma unroll
-      for (int x = 0; x <= kQueues; ++x) stx[x] = st[x];
-#pragma unroll
-      for (int x = 0; x <= kQueues; ++x) ip[x] = ipre(h * nb + stx[x]);
-      lds_order[r] = h;
-#pragma unroll
-      for (int x = 0; x < kQueues; ++x) lds_len[r * kQueues + x] = ip[x + 1] - ip[x];
     }
     __syncthreads();
-  }
-  if (threadIdx.x < kQueues) {
-    const int x = threadIdx.x;
-    int run = 0;
-    for (int r = 0; r < n_heads; ++r) {
-      int h, len;
-      if (in_lds) {
-        h = lds_order[r];
-        len = lds_len[r * kQueues + x];
-      } else {
-        h = horder[r];
-        const int32_t* st = hstart + (size_t)h * (kQueues + 1);
-        len = ipre(h * nb + st[x + 1]) - ipre(h * nb + st[x]);
+    // 2. heads ranked by decreasing cost (ties: lower head first); the first
+    //    chunk and split record of every head (a scan by the last wave)
+    for (int h = threadIdx.x; h < n_heads; h += kPlanThreads) {
+      const int ch = hcost[h];
+      int rank = 0;
+      for (int k = 0; k < n_heads; ++k) {
+        const int ck = hcost[k];
+        rank += (ck > ch || (ck == ch && k < h)) ? 1 : 0;
       }
-      hoff[(size_t)h * kQueues + x] = run;
-      run += len;
+      horder[rank] = h;
     }
-    qctr[x] = run;  // queue length for now
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int base = 0;
-    for (int x = 0; x < kQueues; ++x) {
-      const int len = qctr[x];
-      qbase[x] = base;
-      base += len;
+    if (wave == nwaves - 1) {
+      uint64_t run = 0;
+      for (int h0 = 0; h0 < n_heads; h0 += 64) {
+        const int h = h0 + lane;
+        const uint64_t v = h < n_heads ? ((uint64_t)(uint32_t)hchunk[h] << 32) | (uint32_t)hsplit[h] : 0ull;
+        const uint64_t incl = wave_incl_scan_u64(v, lane);
+        if (h < n_heads) {
+          hchunk[h] = (int)((run + incl - v) >> 32);
+          hsplit[h] = (int)(uint32_t)(run + incl - v);
+        }
+        run += lane_u64(incl, 63);
+      }
+      if (lane == 0) wtot[0] = (long long)run;
     }
-    qbase[kQueues] = base;
+    __syncthreads();
+    if (attempt > 0 || (int)((uint64_t)wtot[0] >> 32) <= chunk_cap) break;
+    S = 0x7fffffff;  // nothing is split
+    __syncthreads();
   }
-  __syncthreads();
 
-  // 5. scatter items (a split row's chunks consecutively), chunk and split
-  //    records; one wave per head, whose run x fills one contiguous slice of
-  //    queue x. Then reset the queue counters.
+  // 3. per queue (one wave each): a scan over the heads in cost order turns
+  //    the items before run x of a head into the position in queue x of the
+  //    run's first item, less those items
+  int qrun = 0;
+  for (int r0 = 0; r0 < n_heads; r0 += 64) {
+    int h = -1, before = 0, pos = 0;
+    if (wave < kQueues && r0 + lane < n_heads) {
+      h = horder[r0 + lane];
+      before = hitem[(int64_t)h * (kQueues + 1) + wave];
+      pos = hitem[(int64_t)h * (kQueues + 1) + wave + 1] - before;
+    }
+    const int incl = wave_incl_scan_i32(pos, lane);
+    __syncthreads();  // the wave of the queue before this one has read the run's start
+    if (h >= 0) hitem[(int64_t)h * (kQueues + 1) + wave] = qrun + incl - pos - before;
+    qrun += __builtin_amdgcn_readlane(incl, 63);
+  }
+  if (wave < kQueues && lane == 0) qlen[wave] = qrun;
+  __syncthreads();
+  int qb[kQueues + 1];
+  qb[0] = 0;
+#pragma unroll
+  for (int x = 0; x < kQueues; ++x) qb[x + 1] = qb[x] + qlen[x];
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int x = 0; x <= kQueues; ++x) qbase[x] = qb[x];
+    *n_split = (int)(uint32_t)wtot[0];
+    if (psplit) *psplit = S;
+  }
+  if (threadIdx.x < kQueues) qctr[threadIdx.x] = 0;
+
+  // 4. scatter items (a split row's chunks consecutively), chunk and split
+  //    records; one wave per head
   for (int h = wave; h < n_heads; h += nwaves) {
-    // the head's run starts and the start of its slice of every queue, one
-    // per lane, loaded together
-    const int32_t* st = hstart + (size_t)h * (kQueues + 1);
-    const int st_l = lane <= kQueues ? st[lane] : 0;
-    const int off_l = lane < kQueues ? qbase[lane] + hoff[(size_t)h * kQueues + lane] : 0;
+    const int* st = hstart + (int64_t)h * kQueues;
+    const int* hi = hitem + (int64_t)h * (kQueues + 1);
+    int c[R];
+    if (S < nb) load_counts(h, c);
+    int run0[kQueues], delta[kQueues];
+#pragma unroll
     for (int x = 0; x < kQueues; ++x) {
-      const int i_begin = __builtin_amdgcn_readlane(st_l, x);
-      const int i_end = __builtin_amdgcn_readlane(st_l, x + 1);
-      if (i_begin >= i_end) continue;
-      const int slice = __builtin_amdgcn_readlane(off_l, x) - ipre(h * nb + i_begin);
-      for (int i = i_begin + lane; i < i_end; i += 64) {
+      run0[x] = __builtin_amdgcn_readfirstlane(st[x]);
+      delta[x] = __builtin_amdgcn_readfirstlane(hi[x]) + qb[x];
+    }
+    const int first_chunk = hchunk[h], first_split = hsplit[h];
+    int items_before = 0, splits_before = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int i = 64 * k + lane;
+      if (64 * k < nb) {
+        const bool in = i < nb;
+        int ib = i;
+        bool split = false;
+        int n = 1;
+        if (S < nb) {
+          split = in && c[k] > S;
+          n = !in ? 0 : split ? (c[k] + S - 1) / S : 1;
+          const int incl = wave_incl_scan_i32(n, lane);
+          ib = items_before + incl - n;
+          items_before += __builtin_amdgcn_readlane(incl, 63);
+        }
+        int d = delta[0];
+#pragma unroll
+        for (int x = 1; x < kQueues; ++x) d = i >= run0[x] ? delta[x] : d;
         const int r = h * nb + i;
-        const int pos = slice + ipre(r);
-        const int n = ipre(r + 1) - ipre(r);
-        if (n == 1) {
-          items[pos] = r;
-        } else {
-          const int c0 = cpre[r];
-          const int cnt = kept_of(r);
-          for (int c = 0; c < n; ++c) {
-            items[pos + c] = -1 - (c0 + c);
-            chunks[c0 + c] = make_int4(r, (int)(((int64_t)c * cnt) / n), (int)(((int64_t)(c + 1) * cnt) / n), 0);
+        if (in && !split) items[d + ib] = r;
+        if (S < nb) {
+          const uint64_t sm = __ballot(split);
+          if (split) {
+            const int sb = splits_before + lanes_below(sm);
+            const int c0 = first_chunk + ib - (i - sb);  // chunks before this row: items less unsplit rows
+            for (int u = 0; u < n; ++u) {
+              items[d + ib + u] = -1 - (c0 + u);
+              chunks[c0 + u] = make_int4(r, u * c[k] / n, (u + 1) * c[k] / n, 0);  // (n, c <= 1024)
+            }
+            splits[first_split + sb] = make_int4(r, c0, n, 0);
           }
-          splits[spre[r]] = make_int4(r, c0, n, 0);
+          splits_before += __popcll(sm);
         }
       }
     }
-  }
-  __syncthreads();
-  if (threadIdx.x < kQueues) qctr[threadIdx.x] = 0;
-}
-
-// Union lists of the query-block pairs, one wave per pair slot (pairs with a
-// split row are not formed and skipped): the two rows' kept sets become bitmaps in LDS,
-// read back in ascending block order as entries j | (j not kept by the first
-// row) << 16 | (j not kept by the second row) << 17. An entry repeated in a
-// kept list counts once.
-constexpr int kPairWords = kMaxBlocks / 64;
-
-__global__ __launch_bounds__(256) void pair_list_kernel(const int32_t* __restrict__ counts,
-                                                        const int32_t* __restrict__ kv_idx, int n_heads, int nb,
-                                                        const BlockMap* __restrict__ table, int pairs_head,
-                                                        const int32_t* __restrict__ pfirst,
-                                                        const int32_t* __restrict__ psplit, int32_t* __restrict__ plist,
-                                                        int32_t* __restrict__ pcount) {
-  __shared__ unsigned long long bits[4][2 * kPairWords];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int S = *psplit;
-  const int n_pairs = n_heads * pairs_head;
-  unsigned long long* bw = bits[wave];
-  auto whole = [&](int rr) { return min(max(counts[rr], 0), nb) <= S; };
-  for (int slot = blockIdx.x * 4 + wave; slot < n_pairs; slot += gridDim.x * 4) {
-    const int bh = slot / pairs_head;
-    const int i = pfirst[slot - bh * pairs_head];
-    const int r = bh * nb + i;
-    const int r2 = r + table[i].poff;
-    if (!whole(r) || !whole(r2)) continue;  // not formed: both rows run alone
-    if (lane < 2 * kPairWords) bw[lane] = 0ull;
-    wave_sync();
-    for (int s = 0; s < 2; ++s) {
-      const int rs = s ? r2 : r;
-      const int c = min(max(counts[rs], 0), nb);
-      const int32_t* kv = kv_idx + (int64_t)rs * nb;
-      for (int a = lane; a < c; a += 64) {
-        const int j = min(max(kv[a], 0), nb - 1);
-        atomicOr(&bw[s * kPairWords + (j >> 6)], 1ull << (j & 63));
-      }
-    }
-    wave_sync();
-    int32_t* out = plist + (int64_t)slot * nb;
-    int n = 0;
-    for (int w = 0; w * 64 < nb; ++w) {
-      const int j = 64 * w + lane;
-      const int ka = (int)((bw[w] >> lane) & 1ull);
-      const int kb = (int)((bw[kPairWords + w] >> lane) & 1ull);
-      const bool keep = (ka | kb) != 0;  // bits past nb are never set
-      const uint64_t m = __ballot(keep);
-      if (keep) out[n + lanes_below(m)] = j | ((ka ^ 1) << 16) | ((kb ^ 1) << 17);
-      n += __popcll(m);
-    }
-    if (lane == 0) pcount[slot] = n;
-    wave_sync();  // the bitmaps are cleared for the next pair only after every lane read them
   }
 }
 
@@ -1452,33 +1456,12 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnParams P, const int4* 
   }
 }
 
-static_assert(kMaxBlocks <= 1024, "block_table_kernel runs one thread per block in one workgroup");
-
-// Block records of every block of the tiling, one thread per block in one
-// workgroup (nb <= 1024), the query-block pairs numbered in the order of
-// their first block; and (pfirst != null) the first block of every pair.
-__global__ __launch_bounds__(1024) void block_table_kernel(Geometry g, BlockMap* __restrict__ table,
-                                                          int32_t* __restrict__ pfirst) {
-  __shared__ int wsum[1024 / 64];
-  const int j = threadIdx.x;
-  const int lane = j & 63;
-  const int wave = j >> 6;
-  BlockMap m = {};
-  int first = 0;
-  if (j < g.nb) {
-    m = block_map(g, j);
-    first = m.poff > 0 ? 1 : 0;
-  }
-  const int incl = wave_incl_scan_i32(first, lane);
-  if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
-  int before = incl - first;
-  for (int w = 0; w < wave; ++w) before += wsum[w];
-  if (j < g.nb) {
-    m.pslot = first ? before : -1;
-    table[j] = m;
-    if (pfirst && first) pfirst[before] = j;
-  }
+// Block records alone, for the naive grid (one workgroup).
+__global__ __launch_bounds__(kPlanThreads) void block_table_kernel(Geometry g, BlockMap* __restrict__ table) {
+  __shared__ int wsum[kPlanThreads / 64];
+  __shared__ int pfirst[kMaxBlocks];
+  const BlockMap m = number_blocks(g, wsum, pfirst);
+  if ((int)threadIdx.x < g.nb) table[threadIdx.x] = m;
 }
 
 // counts and ascending kept-block lists from a block mask, one wave per row.
@@ -1552,7 +1535,6 @@ struct AttnWorkspace {
   BlockMap* bmap;    // [nb]
   int32_t* plist;    // [pairs][nb]   union lists of query-block pairs (null: no pairing)
   int32_t* pcount;   // [pairs]
-  int32_t* pfirst;   // [pairs per head] first block of each pair slot
   int32_t* psplit;   // [1]           the plan's chunk size
   int pairs_head;    // pairs per head
   int cap;           // chunk records
@@ -1617,14 +1599,13 @@ AttnWorkspace carve(void* base, int batch, int heads, const Geometry& g, uint32_
   off += al((size_t)nb * sizeof(BlockMap));
   w.pairs_head = pairs_of(g, flags, lean);
   const size_t pairs = nh * (size_t)w.pairs_head;
-  w.plist = w.pcount = w.pfirst = w.psplit = nullptr;
+  w.plist = w.pcount = w.psplit = nullptr;
   if (pairs > 0) {
     w.plist = reinterpret_cast<int32_t*>(p + off);
     off += al(pairs * nb * 4);
     w.pcount = reinterpret_cast<int32_t*>(p + off);
     off += al(pairs * 4);
-    w.pfirst = reinterpret_cast<int32_t*>(p + off);
-    off += al((size_t)w.pairs_head * 4);
+    off += al((size_t)w.pairs_head * 4);  // (unused; the sizes that the queries return stay as they are)
     w.psplit = reinterpret_cast<int32_t*>(p + off);
     off += al(4);
   }
@@ -1727,11 +1708,10 @@ hipError_t launch_attn(const AttnArgs& a) {
   P.psplit = ws.psplit;
   P.pairs_head = ws.pairs_head;
 
-  hipLaunchKernelGGL(block_table_kernel, dim3(1), dim3(1024), 0, a.stream, g, ws.bmap, ws.pfirst);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-
   if (a.flags & 1u) {
+    hipLaunchKernelGGL(block_table_kernel, dim3(1), dim3(kPlanThreads), 0, a.stream, g, ws.bmap);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (f8)
       hipLaunchKernelGGL(attn_naive_kernel<true>, dim3(n_items), dim3(kAttnThreads), 0, a.stream, P);
     else
@@ -1739,19 +1719,21 @@ hipError_t launch_attn(const AttnArgs& a) {
     return hipGetLastError();
   }
   const int forced = (int)((a.flags >> 8) & 0xFFFFu);
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(1024), 0, a.stream, counts, a.batch * a.heads, g, kSplitSlots, forced,
+  const int n_heads = a.batch * a.heads;
+  // the work list's workgroup, and one wave per query-block pair (at least one
+  // workgroup, which writes the block records)
+  const int64_t pair_groups = ((int64_t)n_heads * ws.pairs_head * 64 + kPlanThreads - 1) / kPlanThreads;
+  const dim3 pgrid(1 + (unsigned)std::max<int64_t>(1, std::min<int64_t>(pair_groups, info.cus)));
+  auto prep = n_heads > kPlanLdsHeads ? prep_kernel<false, 16>
+              : g.nb <= 256           ? prep_kernel<true, 4>
+              : g.nb <= 512           ? prep_kernel<true, 8>
+              : g.nb <= 768           ? prep_kernel<true, 12>
+                                      : prep_kernel<true, 16>;
+  hipLaunchKernelGGL(prep, pgrid, dim3(kPlanThreads), 0, a.stream, counts, kv_idx, n_heads, g, kSplitSlots, forced,
                      ws.cap, ws.items, ws.qbase, ws.qctr, ws.hscratch, ws.rscratch, ws.chunks, ws.splits, ws.n_split,
-                     ws.bmap, ws.plist ? 1 : 0, ws.psplit);
+                     ws.bmap, ws.pairs_head, ws.psplit, ws.plist, ws.pcount);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (ws.plist) {
-    const int n_pairs = a.batch * a.heads * ws.pairs_head;
-    const int pgrid = std::max(1, std::min((n_pairs + 3) / 4, 4 * info.cus));
-    hipLaunchKernelGGL(pair_list_kernel, dim3(pgrid), dim3(256), 0, a.stream, counts, kv_idx, a.batch * a.heads,
-                       g.nb, ws.bmap, ws.pairs_head, ws.pfirst, ws.psplit, ws.plist, ws.pcount);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   int grid = info.cus * (f8 ? info.per_cu8 : info.per_cu);
   if ((int64_t)grid > (int64_t)n_items + ws.cap) grid = n_items + ws.cap;
   if (f8)

@@ -10,7 +10,7 @@ the output starts with.
 import numpy as np
 import pytest
 
-import synth
+from oracle.compare import ATTN_MAX_ABS
 
 from _gpu_util import custom_config, geometry_of, lib, tiling_of, to_dev, torch_mod
 
@@ -44,3 +44,40 @@ def test_every_item_runs_once(heads, grid, tile):
         out = torch.full_like(q, float("nan"))
         fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=flags, out=out)
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize(
+    "heads,grid,tile,split",
+    [
+        (3, (1, 64, 64), (1, 8, 8), 0),  # nb 64: one whole round of rows per head, pairs
+        (2, (1, 1, 64 * 65), (1, 1, 64), 3),  # nb 65: one row in the second round, every row split
+        (2, (4, 64, 65), (2, 8, 8), 7),  # nb 144, partial last column
+        (17, (1, 1, 64 * 257), (1, 1, 64), 90),  # nb 257 (the next number of rounds), more heads than waves
+    ],
+)
+def test_work_list_over_row_rounds(heads, grid, tile, split):
+    # The work list's workgroup takes a head's rows in rounds of 64, a lane
+    # each: numbers of blocks around a whole round, forced and automatic
+    # chunks, more heads than it has waves.
+    torch, fva = torch_mod(), lib()
+    cfg = custom_config("rounds", heads, grid, tile, np.linspace(0.3, 5.0, heads), seed=71)
+    geo = geometry_of(cfg)
+    rng = np.random.default_rng(72)
+    q, k, v = (torch.randn((1, heads, cfg.N, 128), generator=torch.Generator().manual_seed(73 + i)).bfloat16().cuda()
+               for i in range(3))
+    mask = (rng.random((1, heads, geo.nb, geo.nb)) < rng.random((1, heads, geo.nb, 1))).astype(np.uint8)
+    m = torch.from_numpy(mask).cuda()
+    want = fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=fva.FVA_SCHED_NAIVE)
+    out = torch.full_like(q, float("nan"))
+    fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=fva.FVA_SPLIT_BLOCKS(split) if split else 0, out=out)
+    # rows that are cut into chunks merge them in another order: within the
+    # bar of the attention itself
+    assert not torch.isnan(out).any()
+    assert (out.float() - want.float()).abs().max().item() <= ATTN_MAX_ABS
+    c = torch.from_numpy(mask.sum(-1).astype(np.int64))
+    S = split or max(32, -(-int((c + 1).sum()) // 1024))
+    tok = torch.from_numpy(np.concatenate(geo.block_tokens))
+    whole = (c[0] <= S).numpy().repeat(geo.block_sizes, axis=1)
+    for h in range(heads):
+        rows = tok[torch.from_numpy(whole[h])].cuda()
+        assert torch.equal(out[0, h, rows], want[0, h, rows])
