@@ -946,13 +946,18 @@ __device__ __forceinline__ int pair_role(const BlockMap* __restrict__ table, con
 // Each workgroup's first item is given by its index: workgroup b takes entry
 // b / kQueues of queue b % kQueues (workgroup n runs on XCD n % 8), so the
 // first G / kQueues entries of a queue (G workgroups) need no counter, and the
-// workgroups beyond the number of items leave at once. Later items are popped
-// with one atomic from the own queue; once that is empty, the eight counters
-// are read together and only queues that still hold items are popped from.
+// workgroups beyond the number of items leave at once. When there are no more
+// items than workgroups, those whose queue is shorter than that take, in
+// order, the entries that longer queues have left over: no counter is read at
+// all. Otherwise later items are popped with one atomic from the own queue;
+// once that is empty, the eight counters are read with one load and only
+// queues that still hold items are popped from.
 // The counters lie in one cache line that every XCD's atomics meet in memory:
 // with every resident workgroup trying all eight queues (4096 atomics for the
 // 24 items of two heads of a 3x16x16 clip) they held up the working
-// workgroups' tile copies for most of the launch: 64 us, 28 us this way.
+// workgroups' tile copies for most of the launch: 64 us, 28 us with one atomic
+// per item and eight loads at the end of each workgroup. 512 rows of 4 heads
+// (no pairs): 191 us with those eight loads, 181 us with one.
 template <bool F8>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnParams P, const int32_t* __restrict__ items,
                                                                           const int32_t* __restrict__ qbase,
@@ -960,50 +965,68 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
   __shared__ __align__(16) unsigned char ks_tile[kTileBytes];
   __shared__ __align__(16) unsigned char vs_tile[F8 ? kV8TileBytes : kTileBytes];
   __shared__ int next_slot, next_q;
-  const int groups = min((int)gridDim.x, qbase[kQueues]);
+  const int total = qbase[kQueues];
+  const int groups = min((int)gridDim.x, total);
   if ((int)blockIdx.x >= groups) return;
   int q = blockIdx.x % kQueues;
-  // items of queue x that the workgroups' indices give away
+  // items of queue x that the workgroups' indices give away, of len(x)
   auto given = [&](int x) { return (groups - x + kQueues - 1) / kQueues; };
+  auto len = [&](int x) { return qbase[x + 1] - qbase[x]; };
   bool first = true;
   // The trace record of an item is written at the top of the next iteration,
-  // by thread 0 together with the queue pop: the loop then holds a single
-  // region that only thread 0 runs, so the compiler keeps every lane of
-  // every wave on one path through the loop and its barriers.
+  // by the wave that pops: the loop then holds a single region that only one
+  // wave runs, so the compiler keeps every lane of every wave on one path
+  // through the loop and its barriers.
   int64_t prec = -1, pt0 = 0, pt1 = 0, pcyc = 0;
   int ppoff = 0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (;;) {
-    if (threadIdx.x == 0) {
-      if (prec >= 0) trace_record(P, prec, ppoff, pt0, pt1, pcyc);
+    if (wave == 0) {
+      if (prec >= 0 && threadIdx.x == 0) trace_record(P, prec, ppoff, pt0, pt1, pcyc);
       int slot = -1, qq = q;
-      const int b0 = qbase[q], len = qbase[q + 1] - b0, own = given(q);
-      if (first && (int)(blockIdx.x / kQueues) < len) {
-        slot = b0 + (int)(blockIdx.x / kQueues);
-      } else if (len > own) {
-        const int k = own + atomicAdd(&qctr[q], 1);
-        slot = k < len ? b0 + k : -1;
-      }
-      if (slot < 0) {
-        int ctr[kQueues];
-#pragma unroll
-        for (int x = 0; x < kQueues; ++x)
-          ctr[x] = __hip_atomic_load(&qctr[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned left = 0;
-#pragma unroll
-        for (int x = 0; x < kQueues; ++x)
-          left |= given(x) + ctr[x] < qbase[x + 1] - qbase[x] ? 1u << x : 0u;
-        for (int t = 1; t < kQueues && slot < 0; ++t) {
-          const int x = (q + t) % kQueues;
-          if (!((left >> x) & 1u)) continue;
-          const int k = given(x) + atomicAdd(&qctr[x], 1);
-          if (k < qbase[x + 1] - qbase[x]) {
-            slot = qbase[x] + k;
-            qq = x;
+      const int k0 = blockIdx.x / kQueues;
+      if (first && k0 < len(q)) {
+        slot = qbase[q] + k0;
+      } else if (total <= (int)gridDim.x) {
+        if (first) {
+          // this workgroup's number among those without an entry of their own
+          int spare = k0 - len(q);
+          for (int x = 0; x < q; ++x) spare += max(given(x) - len(x), 0);
+          for (int x = 0; x < kQueues && slot < 0; ++x) {
+            const int extra = max(len(x) - given(x), 0);
+            if (spare < extra) slot = qbase[x] + given(x) + spare;
+            spare -= extra;
+          }
+        }
+      } else {
+        auto pop = [&](int x) {
+          int k = 0;
+          if (threadIdx.x == 0) k = atomicAdd(&qctr[x], 1);
+          return given(x) + __builtin_amdgcn_readfirstlane(k);
+        };
+        if (len(q) > given(q)) {
+          const int k = pop(q);
+          if (k < len(q)) slot = qbase[q] + k;
+        }
+        if (slot < 0) {
+          const int x = threadIdx.x % kQueues;
+          const int c = __hip_atomic_load(&qctr[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const uint32_t left = (uint32_t)__ballot(given(x) + c < len(x)) & ((1u << kQueues) - 1u);
+          for (int t = 1; t < kQueues && slot < 0; ++t) {
+            const int y = (q + t) % kQueues;
+            if (!((left >> y) & 1u)) continue;
+            const int k = pop(y);
+            if (k < len(y)) {
+              slot = qbase[y] + k;
+              qq = y;
+            }
           }
         }
       }
-      next_slot = slot;
-      next_q = qq;
+      if (threadIdx.x == 0) {
+        next_slot = slot;
+        next_q = qq;
+      }
     }
     first = false;
     __syncthreads();
@@ -1703,12 +1726,25 @@ hipError_t launch_attn(const AttnArgs& a) {
   P.trace_chunks = 4 * kSplitSlots;
   P.c2 = a.scale * 1.4426950408889634f;
   P.trace = (a.flags & 2u) ? a.trace : nullptr;
-  P.plist = ws.plist;
+  // Pairs are formed when the items left still fill two workgroups per CU: with
+  // fewer, a pair only puts two rows' key blocks one after the other (2 heads
+  // of 12 blocks of 64 tokens: 28 us paired, 20 us alone; 4 heads of 128 such
+  // blocks, 512 rows: 209 and 191 us); from there on a CU runs a pair in about
+  // the time of one of its rows.
+  const int slots = 2 * info.cus;
+  const bool pairs = ws.plist && n_items - a.batch * a.heads * ws.pairs_head >= slots;
+  P.plist = pairs ? ws.plist : nullptr;
   P.pcount = ws.pcount;
   P.psplit = ws.psplit;
-  P.pairs_head = ws.pairs_head;
+  P.pairs_head = pairs ? ws.pairs_head : 0;
 
-  if (a.flags & 1u) {
+  // The naive grid runs the same item body: also for calls whose rows all fit
+  // on the device at once and are too short to be split (no kept list exceeds
+  // the smallest chunk), where the work list would only be waited for: 2 heads
+  // of 12 blocks 19 us instead of 25, 40 heads (480 rows) 29 instead of 54.
+  const int forced = (int)((a.flags >> 8) & 0xFFFFu);
+  const bool whole = a.lean || g.nb <= (forced > 0 ? forced : kMinChunk);
+  if ((a.flags & 1u) || (whole && n_items <= slots)) {
     hipLaunchKernelGGL(block_table_kernel, dim3(1), dim3(kPlanThreads), 0, a.stream, g, ws.bmap);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1718,11 +1754,10 @@ hipError_t launch_attn(const AttnArgs& a) {
       hipLaunchKernelGGL(attn_naive_kernel<false>, dim3(n_items), dim3(kAttnThreads), 0, a.stream, P);
     return hipGetLastError();
   }
-  const int forced = (int)((a.flags >> 8) & 0xFFFFu);
   const int n_heads = a.batch * a.heads;
   // the work list's workgroup, and one wave per query-block pair (at least one
   // workgroup, which writes the block records)
-  const int64_t pair_groups = ((int64_t)n_heads * ws.pairs_head * 64 + kPlanThreads - 1) / kPlanThreads;
+  const int64_t pair_groups = ((int64_t)n_heads * P.pairs_head * 64 + kPlanThreads - 1) / kPlanThreads;
   const dim3 pgrid(1 + (unsigned)std::max<int64_t>(1, std::min<int64_t>(pair_groups, info.cus)));
   auto prep = n_heads > kPlanLdsHeads ? prep_kernel<false, 16>
               : g.nb <= 256           ? prep_kernel<true, 4>
@@ -1731,7 +1766,7 @@ hipError_t launch_attn(const AttnArgs& a) {
                                       : prep_kernel<true, 16>;
   hipLaunchKernelGGL(prep, pgrid, dim3(kPlanThreads), 0, a.stream, counts, kv_idx, n_heads, g, kSplitSlots, forced,
                      ws.cap, ws.items, ws.qbase, ws.qctr, ws.hscratch, ws.rscratch, ws.chunks, ws.splits, ws.n_split,
-                     ws.bmap, ws.pairs_head, ws.psplit, ws.plist, ws.pcount);
+                     ws.bmap, P.pairs_head, ws.psplit, ws.plist, ws.pcount);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   int grid = info.cus * (f8 ? info.per_cu8 : info.per_cu);

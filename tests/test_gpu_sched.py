@@ -1,10 +1,12 @@
 """Work-list edges of the persistent scheduler against the naive grid.
 
-Whatever way items reach the workgroups (a workgroup's first item by its
-index, later ones from the queue counters), every row must be run exactly
-once: with few enough kept blocks that no row is split, the persistent launch
-equals the naive grid bit for bit, and rows left out would keep the NaN that
-the output starts with.
+Whatever way items reach the workgroups (by their index alone when there are
+no more items than workgroups; else a first item by index and later ones from
+the queue counters), every row must be run exactly once: with few enough kept
+blocks that no row is split, the persistent launch equals the naive grid bit
+for bit, and rows left out would keep the NaN that the output starts with.
+Short rows that all fit on the device take the naive grid by themselves; more
+than 32 blocks or more than 512 rows reach the work list.
 """
 
 import numpy as np
@@ -20,12 +22,13 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize(
     "heads,grid,tile",
     [
-        (1, (1, 8, 8), (1, 8, 8)),  # one item, seven empty queues
-        (1, (1, 8, 40), (1, 8, 8)),  # fewer items than queues
-        (3, (1, 8, 24), (1, 8, 8)),  # 9 items: one queue holds two
-        (7, (2, 16, 24), (2, 8, 8)),  # 42 items, uneven queues
-        (40, (1, 16, 52), (1, 8, 8)),  # 560 items: more than two per CU
-        (160, (2, 8, 40), (2, 8, 8)),  # 800 items of five blocks
+        (1, (1, 8, 8), (1, 8, 8)),  # one row
+        (16, (1, 64, 32), (1, 8, 8)),  # 512 rows of 32 blocks: the last without a work list
+        (1, (1, 8, 264), (1, 8, 8)),  # 33 rows of 33 blocks: the first with one
+        (3, (1, 8, 280), (1, 8, 8)),  # 105 rows, uneven queues
+        (12, (2, 16, 168), (2, 8, 8)),  # 504 rows: nearly every workgroup has its own
+        (40, (1, 16, 52), (1, 8, 8)),  # 560 rows: counters
+        (160, (2, 8, 40), (2, 8, 8)),  # 800 rows of five blocks
     ],
 )
 def test_every_item_runs_once(heads, grid, tile):
@@ -37,8 +40,8 @@ def test_every_item_runs_once(heads, grid, tile):
                for i in range(3))
     # uneven rows, some empty (an empty row's output is zero)
     mask = (rng.random((1, heads, geo.nb, geo.nb)) < rng.random((1, heads, geo.nb, 1))).astype(np.uint8)
+    mask[np.cumsum(mask, -1) > 32] = 0  # the smallest automatic chunk: nothing is split
     m = torch.from_numpy(mask).cuda()
-    assert mask.sum(-1).max() <= 32  # the smallest automatic chunk: nothing is split
     want = fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=fva.FVA_SCHED_NAIVE)
     for flags in (0, fva.FVA_SCHED_UNPAIRED):
         out = torch.full_like(q, float("nan"))
