@@ -1077,6 +1077,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
 constexpr int kMinChunk = 32;        // smallest automatic chunk (kept blocks)
 constexpr int kPlanThreads = 1024;   // one thread per block of the tiling
 constexpr int kPlanLdsHeads = 1024;  // heads whose bookkeeping the plan keeps in LDS
+constexpr int kSortHeads = 64;       // heads and rows up to which a queue's items are put in
+constexpr int kSortRows = 8192;      // order of cost, in kClasses classes
+constexpr int kClasses = 16;
 static_assert(kMaxBlocks <= kPlanThreads, "one thread per block");
 
 // Block records of the tiling, one thread per block of one workgroup, with the
@@ -1157,7 +1160,7 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // are issued together, and the plan's passes (four, with a barrier between)
 // exchange only per-head values, in LDS. As three launches, with the plan's
 // values in memory: 18 us for 2 heads of 12 blocks, 44 us for 5 of 308 and 71
-// us for 40 of 660; this way 6, 15 and 44 us.
+// us for 40 of 660; this way 6, 22 and 53 us.
 //
 // Chunks (the split part of the scheduler): with S = `forced` (> 0) or, by
 // default, S = max(kMinChunk, ceil(total / (2 * slots))), total being the sum
@@ -1179,6 +1182,13 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // same head at the same time (its K/V stay in the shared last-level cache)
 // and the resident workgroups of one XCD work on neighbouring query blocks
 // (their kept K/V blocks overlap in L2).
+// Calls of up to kSortRows rows (16 per workgroup slot) run a queue's items in
+// classes of decreasing cost instead, in the order above within a class: with so
+// few items per slot the launch ends when the last long one does. 5 heads of
+// 480p (1540 rows, 257 of them cut in two): 87 % of the slots' time was busy
+// before, 90 % in classes; 1534 -> 1483 us. With more rows there is nothing to
+// gain and the heads' order keeps more of K/V in the caches: 40 heads of 480p
+// (12320 rows) 10534 us, 10642 in classes.
 //
 // Scratch: per head cost, rank, run starts [kQueues], items before each run
 // [kQueues + 1], first chunk and first split record; in LDS up to
@@ -1195,8 +1205,10 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
   __shared__ int lds_head[IN_LDS ? kPlanLdsHeads * (4 + 2 * kQueues + 1) : 1];
   __shared__ int poffs[kMaxBlocks];
   __shared__ long long wtot[nwaves];
-  __shared__ int qlen[kQueues];
+  __shared__ int qlen[kQueues], qstart[kQueues];
   __shared__ unsigned long long bits[nwaves][2 * kPairWords];
+  __shared__ int cls[IN_LDS ? kSortHeads * kQueues * kClasses : 1];  // [head][queue][class] items, then positions
+  __shared__ uint8_t row_info[IN_LDS ? kSortRows : 1];                // class of a row's items | run << 4
   const int nb = g.nb;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1223,6 +1235,9 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
   int* hchunk = IN_LDS ? hitem + n_heads * (kQueues + 1) : rscratch;
   int* hsplit = hchunk + n_heads;
 
+  const bool sorted = IN_LDS && n_heads <= kSortHeads && n_heads * nb <= kSortRows;
+  int S = 0;  // chunk size
+
   // a lane's rows of head h: i = 64k + lane, all loads in flight at once
   // (lanes past the head re-read its last row)
   auto load_counts = [&](int h, int (&c)[R]) {
@@ -1231,6 +1246,27 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
     for (int k = 0; k < R; ++k) c[k] = hc[min(64 * k + lane, nb - 1)];
 #pragma unroll
     for (int k = 0; k < R; ++k) c[k] = min(max(c[k], 0), nb);
+  };
+  // their kept counts, items (0 past the head) and costs
+  auto row_work = [&](int h, int (&c)[R], int (&n)[R], int (&cost)[R]) {
+    const int32_t* hc = counts + (int64_t)h * nb;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int i = min(64 * k + lane, nb - 1);
+      c[k] = hc[i];
+      n[k] = hc[i + poffs[i]];  // the partner's count (an unpaired row's own)
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      c[k] = min(max(c[k], 0), nb);
+      const int p = min(max(n[k], 0), nb);
+      const bool in = 64 * k + lane < nb;
+      const int poff = poffs[min(64 * k + lane, nb - 1)];
+      const int w = poff == 0 || c[k] > S || p > S ? c[k] + 1 : poff > 0 ? max(c[k], p) + 1 : 1;
+      cost[k] = in ? w : 0;
+      n[k] = in ? 1 : 0;
+      if (in && c[k] > S) n[k] = (c[k] + S - 1) / S;
+    }
   };
 
   // 0. chunk size from the total; pair partner offsets (> 0: first of a pair,
@@ -1249,32 +1285,24 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
   long long total = 0;
 #pragma unroll
   for (int w = 0; w < nwaves; ++w) total += wtot[w];
-  int S = forced > 0 ? forced : (int)max((long long)kMinChunk, (total + 2LL * slots - 1) / (2LL * slots));
+  S = forced > 0 ? forced : (int)max((long long)kMinChunk, (total + 2LL * slots - 1) / (2LL * slots));
 
   // 1. per head (one wave): cost, equal-cost runs, the items before each run,
   //    chunks and split rows; a second time without splitting if the chunks
   //    exceed the workspace's records
   for (int attempt = 0;; ++attempt) {
+    const float class_scale = (float)kClasses / (float)(min(S, nb) + 2);
+    if (sorted) {
+      for (int k = threadIdx.x; k < n_heads * kQueues * kClasses; k += kPlanThreads) cls[k] = 0;
+      __syncthreads();
+    }
     for (int h = wave; h < n_heads; h += nwaves) {
-      int c[R], cn[R];
-      const int32_t* hc = counts + (int64_t)h * nb;
-#pragma unroll
-      for (int k = 0; k < R; ++k) {
-        const int i = min(64 * k + lane, nb - 1);
-        c[k] = hc[i];
-        cn[k] = hc[i + poffs[i]];  // the partner's count (an unpaired row's own)
-      }
+      int kept[R], c[R], cn[R];  // kept counts, items, costs
+      row_work(h, kept, c, cn);
       int hsum = 0, spl = 0;
 #pragma unroll
       for (int k = 0; k < R; ++k) {
-        const int own = min(max(c[k], 0), nb), p = min(max(cn[k], 0), nb);
-        const bool in = 64 * k + lane < nb;
-        const int poff = poffs[min(64 * k + lane, nb - 1)];
-        // cn becomes the row's cost, c its items
-        const int cost = poff == 0 || own > S || p > S ? own + 1 : poff > 0 ? max(own, p) + 1 : 1;
-        cn[k] = in ? cost : 0;
-        c[k] = !in ? 0 : own > S ? (own + S - 1) / S : 1;
-        spl += in && own > S ? 1 : 0;
+        spl += c[k] > 0 && kept[k] > S ? 1 : 0;
         hsum += cn[k];
       }
       const uint64_t sums = wave_sum_u64(((uint64_t)(uint32_t)hsum << 32) | (uint32_t)spl);
@@ -1304,6 +1332,14 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
             for (int x = prev + 1; x <= run; ++x) {
               st[x] = i;
               hi[x] = items_before + nincl - c[k];
+            }
+            if (sorted) {
+              // class of one of the row's items, the highest cost first
+              int w = cn[k];
+              if (c[k] > 1) w = (w + c[k] - 1) / c[k];
+              const int cl = kClasses - 1 - min((int)((float)w * class_scale), kClasses - 1);
+              atomicAdd(&cls[(h * kQueues + run) * kClasses + cl], c[k]);
+              row_info[h * nb + i] = (uint8_t)(cl | (run << 4));
             }
           }
           run_last = __builtin_amdgcn_readlane(run, min(63, nb - 1 - 64 * k));
@@ -1356,8 +1392,18 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
   // 3. per queue (one wave each): a scan over the heads in cost order turns
   //    the items before run x of a head into the position in queue x of the
   //    run's first item, less those items
+  //    (sorted: the items of every (class, head) into the position of the first)
   int qrun = 0;
-  for (int r0 = 0; r0 < n_heads; r0 += 64) {
+  if (sorted && wave < kQueues) {
+    int* cx = &cls[((lane < n_heads ? horder[lane] : 0) * kQueues + wave) * kClasses];
+    for (int c = 0; c < kClasses; ++c) {
+      const int n = lane < n_heads ? cx[c] : 0;
+      const int incl = wave_incl_scan_i32(n, lane);
+      if (lane < n_heads) cx[c] = qrun + incl - n;
+      qrun += __builtin_amdgcn_readlane(incl, 63);
+    }
+  }
+  for (int r0 = 0; r0 < n_heads && !sorted; r0 += 64) {
     int h = -1, before = 0, pos = 0;
     if (wave < kQueues && r0 + lane < n_heads) {
       h = horder[r0 + lane];
@@ -1382,6 +1428,13 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
     if (psplit) *psplit = S;
   }
   if (threadIdx.x < kQueues) qctr[threadIdx.x] = 0;
+  if (sorted) {
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int x = 0; x < kQueues; ++x) qstart[x] = qb[x];
+    }
+    __syncthreads();
+  }
 
   // 4. scatter items (a split row's chunks consecutively), chunk and split
   //    records; one wave per head
@@ -1408,23 +1461,31 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
         int n = 1;
         if (S < nb) {
           split = in && c[k] > S;
-          n = !in ? 0 : split ? (c[k] + S - 1) / S : 1;
+          n = in ? 1 : 0;
+          if (split) n = (c[k] + S - 1) / S;
           const int incl = wave_incl_scan_i32(n, lane);
           ib = items_before + incl - n;
           items_before += __builtin_amdgcn_readlane(incl, 63);
         }
-        int d = delta[0];
+        // position of the row's first item
+        int pos = delta[0] + ib;
+        if (sorted) {
+          const int info = in ? row_info[h * nb + i] : 0;
+          const int x = (info >> 4) & 7;
+          if (in) pos = qstart[x] + atomicAdd(&cls[(h * kQueues + x) * kClasses + (info & 15)], n);
+        } else {
 #pragma unroll
-        for (int x = 1; x < kQueues; ++x) d = i >= run0[x] ? delta[x] : d;
+          for (int x = 1; x < kQueues; ++x) pos = i >= run0[x] ? delta[x] + ib : pos;
+        }
         const int r = h * nb + i;
-        if (in && !split) items[d + ib] = r;
+        if (in && !split) items[pos] = r;
         if (S < nb) {
           const uint64_t sm = __ballot(split);
           if (split) {
             const int sb = splits_before + lanes_below(sm);
             const int c0 = first_chunk + ib - (i - sb);  // chunks before this row: items less unsplit rows
             for (int u = 0; u < n; ++u) {
-              items[d + ib + u] = -1 - (c0 + u);
+              items[pos + u] = -1 - (c0 + u);
               chunks[c0 + u] = make_int4(r, u * c[k] / n, (u + 1) * c[k] / n, 0);  // (n, c <= 1024)
             }
             splits[first_split + sb] = make_int4(r, c0, n, 0);
