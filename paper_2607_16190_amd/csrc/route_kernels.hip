@@ -28,6 +28,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "fva_common.h"
 #include "fva_geometry.h"
 #include "fva_internal.h"
@@ -569,16 +571,22 @@ __device__ __forceinline__ int xcd_contiguous(int n, int total) {
 // Raw products qbar_i . kbar_j (the score s_ij times sqrt(128)) of 16 query
 // blocks against every key block with the fp64 MFMA (16x16x4): lane (row
 // l%16, group g = l/16) feeds dim 32g + k of its query row and its key at
-// step k, so the 32 steps sum the full 128-dim dot product. Wave w takes key
-// tiles w, w+4, ... The grid is one-dimensional over (head, query tile); the
-// products go to a row-major [B*H*nb, nb] fp64 buffer.
+// step k, so the 32 steps sum the full 128-dim dot product. The grid is
+// one-dimensional over (head, query tile, part of the keys); wave w of part x
+// takes key tiles 4x + w, 4 (x + parts) + w, ... The products go to a row-major
+// [B*H*nb, nb] fp64 buffer.
+// A wave's tiles are a chain of loads and dependent products (2048 cycles of
+// the fp64 matrix unit each), so calls with too few (head, query tile) pairs to
+// fill the device give each to several workgroups (parts, see launch_route).
 __global__ __launch_bounds__(kScoreThreads, 3) void score_kernel(const double* __restrict__ qbar,
-                                                             const double* __restrict__ kbar, int nb,
+                                                             const double* __restrict__ kbar, int nb, int parts,
                                                              double* __restrict__ scores) {
   const int ntq = (nb + kSelRows - 1) / kSelRows;
   const int L = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int bh = L / ntq;
-  const int tq = L - bh * ntq;  // query tile
+  const int pair = L / parts;
+  const int part = L - pair * parts;
+  const int bh = pair / ntq;
+  const int tq = pair - bh * ntq;  // query tile
   const int i0 = tq * kSelRows;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -632,7 +640,7 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_kernel(const double* _
   // they hide each other's tile loads better than two waves that each
   // double-buffer their tiles.
   double ka[32];
-  for (int t = wave; t < ntiles; t += nwaves) {
+  for (int t = part * nwaves + wave; t < ntiles; t += parts * nwaves) {
     load_tile(t, ka);
     score_tile(t, ka);
   }
@@ -846,8 +854,15 @@ hipError_t launch_route(const RouteArgs& a) {
                      a.stride_b, a.stride_h, a.stride_n, g, qbar, kbar);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(score_kernel, dim3((g.nb + kSelRows - 1) / kSelRows * bhs), dim3(kScoreThreads), 0, a.stream,
-                     qbar, kbar, g.nb, scores);
+  // Key parts per (head, query tile): up to four workgroups per CU of a 256-CU
+  // device (what its registers hold), at least one key tile per wave. Score
+  // kernel of 5 heads of 480p (100 pairs) 15.5 us in one part, 6.5 us in five; 5
+  // heads of 720p (210 pairs) 30 us, 18 us in four; from 513 pairs on one part.
+  const int score_pairs = (g.nb + kSelRows - 1) / kSelRows * bhs;
+  const int key_tiles = padded_blocks(g.nb) / 16;
+  const int parts = std::max(1, std::min(1024 / score_pairs, (key_tiles + 3) / 4));
+  hipLaunchKernelGGL(score_kernel, dim3(score_pairs * parts), dim3(kScoreThreads), 0, a.stream, qbar, kbar, g.nb,
+                     parts, scores);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int kpl = (g.nb + 63) / 64;
