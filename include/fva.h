@@ -80,13 +80,15 @@ typedef struct fva_qkv_desc {
 } fva_qkv_desc;
 
 /* fva_attn flags. */
-#define FVA_SCHED_PERSISTENT 0u /* persistent grid pulling (head, query-block) items, heaviest first */
+#define FVA_SCHED_PERSISTENT 0u /* persistent grid pulling (head, query-block) items, heaviest first; calls whose
+                                   rows all fit on the device at once and are too short to be split run as the
+                                   naive grid (the same output bit for bit) */
 #define FVA_SCHED_NAIVE 1u      /* one workgroup per item in head-major order (same kernel body) */
 #define FVA_TRACE 2u            /* record per-item start/end clock and CU id into `trace` */
 /* Persistent scheduler only: run every query block as an item of its own.
  * Without it, two neighbouring query blocks that both hold at most 64 real
- * tokens and are both unsplit run as one 128-row item over the union of
- * their kept lists (each block on two of the four waves, each wave skipping
+ * tokens and are both unsplit run (where the items left still fill the
+ * device) as one 128-row item over the union of their kept lists (each block on two of the four waves, each wave skipping
  * the key blocks its block does not keep), so that every K/V tile either
  * keeps is staged once. Neighbours are x-neighbours (ix, ix + 1), ix even,
  * of one (t, y) line; among the blocks no such pair holds, y-neighbours
@@ -262,10 +264,11 @@ fva_status fva_attn(const void* Q, const void* K, const void* V, const fva_qkv_d
 #define FVA_TO_CURVE 0   /* dst[.., r, :] = src[.., perm[r], :] */
 #define FVA_FROM_CURVE 1 /* dst[.., perm[r], :] = src[.., r, :] */
 
-/* Workspace bytes of fva_curve_order: a bitmap of 8^k bits and its word
- * prefix sums (each max(1, 8^k / 32) * 4 bytes) and one uint32 curve index
- * per token, each part 256-byte aligned. FVA_ERR_SHAPE for a non-positive
- * extent, FVA_ERR_UNSUPPORTED for an extent above 256. Host only. */
+/* Workspace bytes of fva_curve_order: twice max(1, 8^k / 32) * 4 bytes and 4
+ * bytes per token, each part 256-byte aligned. The ranks are computed without
+ * scratch; the call still checks for a workspace of this size. FVA_ERR_SHAPE
+ * for a non-positive extent, FVA_ERR_UNSUPPORTED for an extent above 256. Host
+ * only. */
 fva_status fva_curve_workspace_size(int32_t T, int32_t H, int32_t W, size_t* bytes);
 
 /*
@@ -362,8 +365,8 @@ fva_status fva_attn_fp8v(const void* Q, const void* K, const uint8_t* V8, const 
  * Differences from fva_attn: counts and kv_idx are required (in the layout
  * fva_route writes; the mask itself is not read); flags may hold FVA_TRACE
  * only (FVA_SCHED_NAIVE, FVA_SCHED_UNPAIRED and FVA_SPLIT_BLOCKS are
- * rejected); every query block runs as its own item (no query-block pairs,
- * whose union lists are not kept; pairing changes no output bit); no row is
+ * rejected); query-block pairs are formed only where their union lists fit the
+ * scratch behind what a shape needs (pairing changes no output bit); no row is
  * split into chunks, so where fva_attn's automatic chunk size would split rows
  * (few rows per workgroup slot) the output can differ from fva_attn's in the
  * last bits (the same sums in another order); everywhere else it is
@@ -375,7 +378,7 @@ fva_status fva_attn_fp8v(const void* Q, const void* K, const uint8_t* V8, const 
  * part rounded up to 256 bytes: with nb = 660 about 2,000 heads fit. A
  * shape needing more returns FVA_ERR_SCRATCH before anything is launched.
  * Every call on one device shares that
- * device's scratch, and the plan kernel rewrites all of it on every call:
+ * device's scratch, and the call's first kernel rewrites it every time:
  * calls that overlap on one device (different streams, or host threads)
  * race and give undefined results; calls in one stream order are safe.
  */

@@ -1650,16 +1650,16 @@ int chunk_cap(int batch, int heads, int nb, uint32_t flags) {
   return (int)std::min<int64_t>(cap, (int64_t)1 << 28);
 }
 
-// Query-block pairs per head under these flags: none for the naive grid,
-// under FVA_SCHED_UNPAIRED and in the allocation-free call.
-int pairs_of(const Geometry& g, uint32_t flags, bool lean) {
-  return (lean || (flags & 5u)) ? 0 : pairs_per_head(g);
-}
+// Query-block pairs per head under these flags: none for the naive grid and
+// under FVA_SCHED_UNPAIRED.
+int pairs_of(const Geometry& g, uint32_t flags) { return (flags & 5u) ? 0 : pairs_per_head(g); }
 
 // lean: the layout of the allocation-free call -- no room for rebuilt counts
-// and kept lists (the caller passes them), no chunk items (no row is split,
-// so no partial results are kept) and no query-block pairs.
-AttnWorkspace carve(void* base, int batch, int heads, const Geometry& g, uint32_t flags, bool lean = false) {
+// and kept lists (the caller passes them) and no chunk items (no row is split,
+// so no partial results are kept); bytes is what it cannot do without, and the
+// union lists of query-block pairs lie behind that when `room` holds them too.
+AttnWorkspace carve(void* base, int batch, int heads, const Geometry& g, uint32_t flags, bool lean = false,
+                    size_t room = 0) {
   const int nb = g.nb;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t rows = (size_t)batch * heads * nb;
@@ -1693,7 +1693,8 @@ AttnWorkspace carve(void* base, int batch, int heads, const Geometry& g, uint32_
   off += al(cap * kPartialFloats * sizeof(float));
   w.bmap = reinterpret_cast<BlockMap*>(p + off);
   off += al((size_t)nb * sizeof(BlockMap));
-  w.pairs_head = pairs_of(g, flags, lean);
+  const size_t needed = off;
+  w.pairs_head = pairs_of(g, flags);
   const size_t pairs = nh * (size_t)w.pairs_head;
   w.plist = w.pcount = w.psplit = nullptr;
   if (pairs > 0) {
@@ -1706,6 +1707,13 @@ AttnWorkspace carve(void* base, int batch, int heads, const Geometry& g, uint32_
     off += al(4);
   }
   w.bytes = off;
+  if (lean) {
+    w.bytes = needed;
+    if (off > room) {
+      w.pairs_head = 0;
+      w.plist = w.pcount = w.psplit = nullptr;
+    }
+  }
   return w;
 }
 }  // namespace
@@ -1759,7 +1767,7 @@ hipError_t launch_attn(const AttnArgs& a) {
   const Geometry g = make_geometry(a.T, a.H, a.W, a.bt, a.bh, a.bw);
   const int n_items = a.batch * a.heads * g.nb;
   if (n_items == 0) return hipSuccess;
-  const AttnWorkspace ws = carve(a.workspace, a.batch, a.heads, g, a.flags, a.lean);
+  const AttnWorkspace ws = carve(a.workspace, a.batch, a.heads, g, a.flags, a.lean, kNoAllocScratchBytes);
   int32_t* ws_counts = ws.counts;
   int32_t* ws_kv = ws.kv;
   DeviceInfo info;
