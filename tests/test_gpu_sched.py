@@ -23,6 +23,7 @@ pytestmark = pytest.mark.gpu
     "heads,grid,tile",
     [
         (1, (1, 8, 8), (1, 8, 8)),  # one row
+        (8, (8, 16, 32), (2, 8, 8)),  # 256 full rows: the most that run on eight waves each
         (16, (1, 64, 32), (1, 8, 8)),  # 512 rows of 32 blocks: the last without a work list
         (1, (1, 8, 264), (1, 8, 8)),  # 33 rows of 33 blocks: the first with one
         (3, (1, 8, 280), (1, 8, 8)),  # 105 rows, uneven queues
@@ -84,3 +85,29 @@ def test_work_list_over_row_rounds(heads, grid, tile, split):
     for h in range(heads):
         rows = tok[torch.from_numpy(whole[h])].cuda()
         assert torch.equal(out[0, h, rows], want[0, h, rows])
+
+
+@pytest.mark.parametrize("v", ["bf16", "e4m3"])
+@pytest.mark.parametrize("grid,tile", [((3, 9, 13), (2, 8, 8)), ((1, 1, 1000), (1, 1, 128)), ((2, 8, 12), (1, 8, 8))])
+def test_eight_waves_equal_four(v, grid, tile):
+    # Up to a row per CU runs on eight waves of one query tile, more rows on four
+    # of two: the same heads give the same bits alone and among others, for
+    # blocks of every number of tiles (8 .. 128 tokens).
+    torch, fva = torch_mod(), lib()
+    heads = 72  # 72 x 8 (or 12) rows, then the first two heads of them alone
+    cfg = custom_config("waves", heads, grid, tile, np.linspace(0.3, 5.0, heads), seed=91)
+    geo = geometry_of(cfg)
+    rng = np.random.default_rng(92)
+    q, k, w = (torch.randn((1, heads, cfg.N, 128), generator=torch.Generator().manual_seed(93 + i)).bfloat16().cuda()
+               for i in range(3))
+    mask = torch.from_numpy((rng.random((1, heads, geo.nb, geo.nb)) < 0.6).astype(np.uint8)).cuda()
+    assert heads * geo.nb > 256 >= 2 * geo.nb
+
+    def attend(n):
+        qn, kn, wn, mn = (x[:, :n].contiguous() for x in (q, k, w, mask))
+        if v == "bf16":
+            return fva.fva_attn(qn, kn, wn, tiling_of(cfg), mn, flags=fva.FVA_SCHED_NAIVE)
+        return fva.fva_attn_fp8v(qn, kn, *fva.fva_quantize_v(wn, tiling_of(cfg)), tiling_of(cfg), mn,
+                                 flags=fva.FVA_SCHED_NAIVE)
+
+    assert torch.equal(attend(2), attend(heads)[:, :2])
