@@ -230,23 +230,23 @@ def cpu_baseline(cfg, Qb, Kb, Vb, mask, counts, budget_s=20.0, blocks="box"):
 # counter reads for a device copy of known size; valid only for the attention
 # source with this digest (null otherwise).
 ATTN_TRAFFIC = {
-    "source_digest": "f8dc17fcc7ddf8c6",
+    "source_digest": "ee6f1d3d2419015c",
     "bytes": {
-        "720p": ((111222344 + 111111162) // 2 * 2 + 758186) * 1024,
-        "720p-hilbert": ((77795484 + 77549784) // 2 * 2 + 758302) * 1024,
-        "720p-fp8v": ((71772201 + 70525558) // 2 * 2 + 758575) * 1024,
-        "720p-hilbert-fp8v": ((66644817 + 67124268) // 2 * 2 + 758497) * 1024,
+        "720p": ((106332992 + 107636997) // 2 * 2 + 757000) * 1024,
+        "720p-hilbert": ((78494147 + 78194246) // 2 * 2 + 757152) * 1024,
+        "720p-fp8v": ((70670733 + 70880901) // 2 * 2 + 759442) * 1024,
+        "720p-hilbert-fp8v": ((66930490 + 66836343) // 2 * 2 + 759372) * 1024,
     },
 }
 # Same for fva_route (pool_kernel + score_kernel + select_kernel), per call
 # (FETCH x 2, WRITE x 1, KiB per dispatch summed over the three kernels).
 ROUTE_TRAFFIC = {
-    "source_digest": "d8fe57f482ee46fc",
+    "source_digest": "2424d22d3bd8d3a4",
     "bytes": {
-        "720p": ((756175 + 29245 + 68473) * 2 + 53760 + 142312 + 49285) * 1024,
-        "720p-hilbert": ((756151 + 25345 + 55227) * 2 + 47360 + 116782 + 39989) * 1024,
-        "720p-fp8v": ((756173 + 29198 + 68476) * 2 + 53760 + 142496 + 49285) * 1024,
-        "720p-hilbert-fp8v": ((756150 + 25344 + 55238) * 2 + 47360 + 116986 + 39989) * 1024,
+        "720p": ((756153 + 29370 + 68497) * 2 + 53760 + 142321 + 49285) * 1024,
+        "720p-hilbert": ((756145 + 25392 + 55237) * 2 + 47360 + 116771 + 39989) * 1024,
+        "720p-fp8v": ((756161 + 29400 + 68482) * 2 + 53760 + 142149 + 49285) * 1024,
+        "720p-hilbert-fp8v": ((756141 + 25391 + 55238) * 2 + 47360 + 116890 + 39989) * 1024,
     },
 }
 

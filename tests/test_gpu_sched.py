@@ -111,3 +111,21 @@ def test_eight_waves_equal_four(v, grid, tile):
                                  flags=fva.FVA_SCHED_NAIVE)
 
     assert torch.equal(attend(2), attend(heads)[:, :2])
+
+
+@pytest.mark.parametrize("heads", [20, 40])  # union lists of 10.5 MB, and of 21 MB: more than the scratch
+def test_noalloc_pairs_where_they_fit(heads):
+    torch, fva = torch_mod(), lib()
+    cfg = custom_config("fit", heads, (1, 128, 256), (1, 8, 8), np.ones(heads), seed=95)  # 512 blocks, 256 pairs per head
+    nb = geometry_of(cfg).nb
+    gen = torch.Generator(device="cuda").manual_seed(96)
+    q, k, v = (torch.randn((1, heads, cfg.N, 128), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = (torch.rand((1, heads, nb, nb), generator=gen, device="cuda") < 0.02).to(torch.uint8)
+    mask *= (mask.cumsum(-1) <= 32).to(torch.uint8)  # nothing is split
+    counts = mask.sum(-1, dtype=torch.int32)
+    ids = torch.arange(nb, device="cuda", dtype=torch.int32)
+    kv = torch.where(mask.bool(), ids, ids + nb).sort(-1).values.contiguous()
+    kv = torch.where(kv < nb, kv, torch.zeros_like(kv))
+    out = torch.full_like(q, float("nan"))
+    fva.fva_attn_noalloc(q, k, v, tiling_of(cfg), counts, kv, out)
+    assert torch.equal(out, fva.fva_attn(q, k, v, tiling_of(cfg), mask, counts, kv))
