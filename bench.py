@@ -230,7 +230,7 @@ def cpu_baseline(cfg, Qb, Kb, Vb, mask, counts, budget_s=20.0, blocks="box"):
 # counter reads for a device copy of known size; valid only for the attention
 # source with this digest (null otherwise).
 ATTN_TRAFFIC = {
-    "source_digest": "ee6f1d3d2419015c",
+    "source_digest": "2f3037edb6dfe87c",
     "bytes": {
         "720p": ((106332992 + 107636997) // 2 * 2 + 757000) * 1024,
         "720p-hilbert": ((78494147 + 78194246) // 2 * 2 + 757152) * 1024,

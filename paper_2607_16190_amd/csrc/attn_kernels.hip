@@ -959,8 +959,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_naive_kernel(AttnParams P) {
 }
 
 // Persistent scheduler. The work list holds kQueues queues, one per XCD;
-// workgroups pull from the queue of the XCD they run on and steal from the
-// others once theirs is empty.
+// workgroups pull from the queue of the XCD that their index is dealt to and
+// steal from the others once theirs is empty.
 constexpr int kQueues = 8;
 
 // Role of row r (= bh * nb + i) under query-block pairing with chunk size S:
@@ -968,7 +968,7 @@ constexpr int kQueues = 8;
 // when it is the second row of a pair (its item does nothing), 0 otherwise.
 // A pair is formed only when neither row is split (kept count <= S). The
 // persistent kernel decides it with this function, from the block records'
-// partner offsets; the plan and the pair-list kernel apply the same test.
+// partner offsets; prep_kernel's plan applies the same test.
 __device__ __forceinline__ int pair_role(const BlockMap* __restrict__ table, const int32_t* __restrict__ counts,
                                          int r, int i, int S, int nb) {
   auto whole = [&](int rr) { return min(max(counts[rr], 0), nb) <= S; };
