@@ -821,6 +821,14 @@ __device__ void process_item(const AttnParams& P, int row, int begin, int end, f
       j1 = j2;
     }
   } else {
+  // The loop's first instruction lies 16 bytes past a 32-byte boundary (three
+  // nops and the four bytes more that the moves between them and the loop take):
+  // its time depends on where its products fall in the 32-byte instruction
+  // fetches. Over the eight placements 4 bytes apart, 16 heads of a 111,600-token
+  // clip took 17.60 (16 and 20 bytes past) to 17.84 ms (12 past), 16 heads of 720p
+  // 23.19 to 23.43. Without this line the code before the loop decides, and a
+  // change there cost 0.2 to 1 % of every large call.
+  asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
   for (int c = 0; c < cnt; ++c) {
     const int nj = mc.n;
     const int ng = ngroups_of(nj);

@@ -1,0 +1,70 @@
+"""Where the block loop of the bf16 attention kernels lies in the built library.
+
+The loop's time depends on where its instructions fall in the 32-byte fetches
+(1.5 % between the best and the worst of the eight placements), and code before
+the loop moves it: the source pads it to 16 bytes past a 32-byte boundary.
+The library's own gfx950 code object is disassembled and the loop's first
+instruction looked up: the target of the shortest backward branch that spans
+all matrix instructions of the kernel.
+"""
+
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2607_16190_amd as fva
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects(path):
+    """gfx950 code objects of a library's offload bundles."""
+    data = open(path, "rb").read()
+    at = data.find(MAGIC)
+    while at >= 0:
+        (n,) = struct.unpack_from("<Q", data, at + len(MAGIC))
+        p = at + len(MAGIC) + 8
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", data, p)
+            triple = data[p + 24 : p + 24 + length].decode()
+            p += 24 + length
+            if triple.endswith("gfx950") and size:
+                yield data[at + off : at + off + size]
+        at = data.find(MAGIC, at + 1)
+
+
+def kernel_code(tmp_path, name):
+    """[(address, instruction, branch target or None)] of the kernel whose mangled name holds `name`."""
+    for i, obj in enumerate(code_objects(fva.LIB_PATH)):
+        if name.encode() not in obj:
+            continue
+        path = tmp_path / f"{i}.co"
+        path.write_bytes(obj)
+        text = subprocess.run([OBJDUMP, "-d", str(path)], capture_output=True, text=True, check=True).stdout
+        m = re.search(r"^([0-9a-f]+) <\w*%s\w*>:\n(.*?)(?:\n\n|\Z)" % name, text, re.S | re.M)
+        if not m:
+            continue
+        base, code = int(m.group(1), 16), []
+        for line in m.group(2).split("\n"):
+            x = re.match(r"\s+(\S+).*//\s*([0-9A-F]+):.*?(?:<\w+\+0x([0-9a-f]+)>)?\s*$", line)
+            if x:
+                code.append((int(x.group(2), 16), x.group(1), base + int(x.group(3), 16) if x.group(3) else None))
+        return code
+    return None
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+@pytest.mark.parametrize("kernel", ["attn_persistent_kernelILb0E"])
+def test_block_loop_starts_16_bytes_past_a_fetch(kernel, tmp_path):
+    code = kernel_code(tmp_path, kernel)
+    assert code, f"{kernel} not found in {fva.LIB_PATH}"
+    products = [a for a, op, _ in code if "mfma" in op]
+    assert len(products) > 100
+    loops = [(a - t, t) for a, op, t in code
+             if t is not None and op.startswith(("s_branch", "s_cbranch")) and t < products[0] and a > products[-1]]
+    assert loops
+    assert min(loops)[1] % 32 == 16
