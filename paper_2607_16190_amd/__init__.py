@@ -218,10 +218,12 @@ def fva_trace_words(desc: _Desc, tiling: Tiling) -> int:
 
 def _stream_ptr(stream):
     """Raw stream to launch on. The current stream's pointer is asked for directly: building the
-    torch.cuda.Stream object that carries it takes 2.9 us, a third of a call's host time."""
+    torch.cuda.Stream object that carries it takes 2.9 us, a third of a call's host time. The
+    accessor is not part of torch's public interface; a torch without it gets the object."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _workspace(nbytes: int, device, workspace):
