@@ -322,7 +322,7 @@ def fva_attn(q, k, v, tiling: Tiling, mask, counts=None, kv_idx=None, *, scale: 
         raise ValueError("FVA_TRACE needs a trace tensor of fva_trace_words int64")
     st = lib.fva_attn(
         _ptr(q), _ptr(k), _ptr(v), ctypes.byref(desc), ctypes.byref(tiling.c()), _ptr(mask), _ptr(counts),
-        _ptr(kv_idx), float(scale), int(flags), _ptr(out), _ptr(ws),
+        _ptr(kv_idx), ctypes.c_float(scale), int(flags), _ptr(out), _ptr(ws),
         ws.numel() * ws.element_size(), _ptr(trace), _stream_ptr(stream),
     )
     _check(st, "fva_attn")
@@ -347,7 +347,7 @@ def fva_attn_noalloc(q, k, v, tiling: Tiling, counts, kv_idx, out, *, scale: flo
     desc = _desc_of(q)
     st = lib.fva_attn_noalloc(
         _ptr(q), _ptr(k), _ptr(v), ctypes.byref(desc), ctypes.byref(tiling.c()), _ptr(counts), _ptr(kv_idx),
-        float(scale), int(flags), _ptr(out), _ptr(trace), _stream_ptr(stream),
+        ctypes.c_float(scale), int(flags), _ptr(out), _ptr(trace), _stream_ptr(stream),
     )
     _check(st, "fva_attn_noalloc")
     return out
@@ -446,7 +446,7 @@ def fva_attn_fp8v(q, k, v8, vexp, tiling: Tiling, mask, counts=None, kv_idx=None
         raise ValueError("FVA_TRACE needs a trace tensor of fva_trace_words int64")
     st = lib.fva_attn_fp8v(
         _ptr(q), _ptr(k), _ptr(v8), _ptr(vexp), ctypes.byref(desc), ctypes.byref(tiling.c()), _ptr(mask),
-        _ptr(counts), _ptr(kv_idx), float(scale), int(flags), _ptr(out), _ptr(ws),
+        _ptr(counts), _ptr(kv_idx), ctypes.c_float(scale), int(flags), _ptr(out), _ptr(ws),
         ws.numel() * ws.element_size(), _ptr(trace), _stream_ptr(stream),
     )
     _check(st, "fva_attn_fp8v")
