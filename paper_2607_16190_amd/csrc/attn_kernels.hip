@@ -1909,9 +1909,10 @@ hipError_t launch_attn(const AttnArgs& a) {
                        ws.qbase, ws.qctr);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // Split rows (if any) are merged; the workgroups beyond their number exit.
-  if (g.nb > (forced > 0 ? forced : kMinChunk)) {
-    const int cgrid = std::max(1, (int)std::min<int64_t>(2 * (int64_t)ws.cap, 4 * info.cus));
+  // Split rows (if any) are merged; the workgroups beyond their number exit. A
+  // call without chunk records (the allocation-free one) splits none.
+  if (ws.cap > 0 && g.nb > (forced > 0 ? forced : kMinChunk)) {
+    const int cgrid = (int)std::min<int64_t>(2 * (int64_t)ws.cap, 4 * info.cus);
     hipLaunchKernelGGL(combine_kernel, dim3(cgrid), dim3(256), 0, a.stream, P, ws.splits, ws.n_split);
     e = hipGetLastError();
   }

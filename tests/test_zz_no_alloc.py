@@ -8,6 +8,8 @@ attention bar (max 2e-2, mean 1e-3 against the fp64 oracle) where its
 automatic chunk size splits rows that the allocation-free call keeps whole.
 """
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -107,3 +109,31 @@ def test_noalloc_trace_and_repeat():
     tr = trace.view(-1, 4).cpu().numpy()
     rows = cfg.heads * geometry_of(cfg).nb
     assert np.all(tr[:rows, 0] > 0) and np.all(tr[:rows, 1] >= tr[:rows, 0]) and not tr[rows:].any()
+
+
+def test_noalloc_graph_holds_two_launches():
+    # No row of the allocation-free call is split: the work list and the
+    # attention are all it launches, and replays of the captured pair follow
+    # the inputs' contents.
+    torch, fva = torch_mod(), lib()
+    cfg = custom_config("captured", 6, (4, 32, 96), (1, 8, 8), np.linspace(0.5, 4.0, 6), seed=25)
+    Qb, Kb, Vb = synth.gen_qkv(cfg)
+    q, k, v, mask, counts, kv = routed(cfg, Qb, Kb, Vb)
+    assert q.shape[1] * counts.shape[2] > 512 and counts.shape[2] > 32  # a work list, rows long enough to be split
+    out = torch.empty_like(q)
+    fva.fva_attn_noalloc(q, k, v, tiling_of(cfg), counts, kv, out)  # (the first call finds the scratch's address)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fva.fva_attn_noalloc(q, k, v, tiling_of(cfg), counts, kv, out)
+    hip = ctypes.CDLL(fva.LIB_PATH)  # (and the HIP runtime it is bound to)
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == 2
+    graph.instantiate()
+    for scale in (1.0, -2.0, 0.5):
+        v.copy_(to_dev(Vb) * scale)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, noalloc(q, k, v, cfg, counts, kv))
