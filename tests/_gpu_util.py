@@ -45,6 +45,15 @@ def workload(name: str):
     return synth.gen_qkv(synth.get_config(name))
 
 
+def work_list_heads(rows, *tensors):
+    """The heads (axis 1) of a small call's tensors so many times over that the
+    call no longer takes the plain grid and forms query-block pairs: at least
+    1024 rows of `rows` each time, 512 items with every pair formed. Returns the
+    number of copies and the tensors."""
+    copies = -(-1024 // rows)
+    return copies, [x.repeat(1, copies, *[1] * (x.dim() - 2)) for x in tensors]
+
+
 def custom_config(name, heads, grid, tile, alphas, seed, p=0.9, k_min=4):
     return synth.WorkloadConfig(name, heads, grid, tile, p, k_min, seed, "fixed", tuple(alphas))
 

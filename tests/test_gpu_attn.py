@@ -28,6 +28,7 @@ from _gpu_util import (
     tiling_of,
     to_dev,
     torch_mod,
+    work_list_heads,
     workload,
 )
 
@@ -72,6 +73,9 @@ def test_attn_tiny_routed_mask_both_schedulers():
     O_n = run_attn(q, k, v, cfg, mask, counts, kv, flags=fva.FVA_SCHED_NAIVE)
     O_m = run_attn(q, k, v, cfg, mask)  # counts / kv_idx rebuilt from the mask
     assert torch_mod().equal(O_p, O_n) and torch_mod().equal(O_p, O_m)
+    # 24 rows take the plain grid whatever the flags; more of the same heads the work list
+    n, (qn, kn, vn, *lists) = work_list_heads(counts.numel(), q, k, v, mask, counts, kv)
+    assert torch_mod().equal(run_attn(qn, kn, vn, cfg, *lists), O_p.repeat(1, n, 1, 1))
     compare_full("tiny", Qb, Kb, Vb, cfg, mask.cpu().numpy(), o64(O_p))
 
 
@@ -117,6 +121,8 @@ def test_attn_host_masks(kind, grid, tile):
     O = run_attn(q, k, v, cfg, mt)
     O_n = run_attn(q, k, v, cfg, mt, flags=fva.FVA_SCHED_NAIVE)
     assert torch.equal(O, O_n)
+    n, (qn, kn, vn, mn) = work_list_heads(2 * geo.nb, q, k, v, mt)
+    assert torch.equal(run_attn(qn, kn, vn, cfg, mn), O.repeat(1, n, 1, 1))  # the work list, with pairs
     Of = o64(O)
     compare_full(f"{kind} grid{grid}", Qb, Kb, Vb, cfg, mask, Of)
     if kind == "empty_rows":
@@ -236,6 +242,9 @@ def test_attn_batch_two_odd_heads():
     O_m = run_attn(q, k, v, cfg, mask)
     torch = torch_mod()
     assert torch.equal(O_p, O_n) and torch.equal(O_p, O_m)
+    # 108 rows take the plain grid; an odd number of heads on the work list too
+    n, (qn, kn, vn, *lists) = work_list_heads(counts.numel(), q, k, v, mask, counts, kv)
+    assert torch.equal(run_attn(qn, kn, vn, cfg, *lists), O_p.repeat(1, n, 1, 1))
     compare_full("batch2", Qb, Kb, Vb, cfg, mask.cpu().numpy(), o64(O_p))
 
 

@@ -40,6 +40,7 @@ from _gpu_util import (
     tiling_of,
     to_dev,
     torch_mod,
+    work_list_heads,
     workload,
 )
 
@@ -156,6 +157,11 @@ def test_fp8_attn_tiny_both_schedulers_and_rebuilt_lists():
     O_n = fp8_attn(Qb, Kb, Vb, tiling, mask, counts, kv, flags=fva.FVA_SCHED_NAIVE)
     O_m = fp8_attn(Qb, Kb, Vb, tiling, mask)
     assert np.array_equal(O_p, O_n) and np.array_equal(O_p, O_m)  # same item body, same order
+    # 24 rows take the plain grid whatever the flags; more of the same heads the work list
+    n, (qn, kn, w8, wexp, *lists) = work_list_heads(counts.numel(), to_dev(Qb), to_dev(Kb),
+                                                    *fva.fva_quantize_v(to_dev(Vb), tiling), mask, counts, kv)
+    O_w = fva.fva_attn_fp8v(qn, kn, w8, wexp, tiling, *lists)
+    assert np.array_equal(O_w.float().cpu().numpy(), np.tile(O_p, (1, n, 1, 1)))
     O_s = fp8_attn(Qb, Kb, Vb, tiling, mask, counts, kv, flags=fva.FVA_SPLIT_BLOCKS(2))
     compare_rows("tiny split 2", Qb, Kb, Vb, m, O_s[0], geo, rows)
 

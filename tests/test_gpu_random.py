@@ -16,6 +16,11 @@ to 1 and k_min from 0 to 6. For each case:
   tests/test_gpu_curve.py, batch 0);
 * routing with slack-aware augmentation over a random head -> rank map,
   bit-exact (tests/test_gpu_sasa.py).
+
+Calls this small take the plain grid. So every output that is checked against
+the oracle is also compared with the work list's: the same heads repeated until
+the items fill the device (pairs included), equal bit for bit, and with rows cut
+into chunks, within the same bars.
 """
 
 import numpy as np
@@ -25,7 +30,7 @@ import synth
 from oracle import attn_ref_head, route_ref
 from oracle.compare import ATTN_MAX_ABS, ATTN_MEAN_ABS, compare_mask_rows
 
-from _gpu_util import f64, geometry_of, lib, log, tiling_of, to_dev, torch_mod
+from _gpu_util import f64, geometry_of, lib, log, tiling_of, to_dev, torch_mod, work_list_heads
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +49,17 @@ def draw(case):
     return synth.WorkloadConfig(f"random{case}", heads, grid, tile, p, k_min, 700 + case, "fixed", alphas, batch=batch)
 
 
+def over_the_work_list(attend, tensors, geo, out):
+    """attend(flags, *tensors) runs a drawn case: with its heads repeated, whole rows and pairs on the work list, its
+    output must be `out`, the plain grid's. Returns its outputs with rows cut into chunks."""
+    fva, torch = lib(), torch_mod()
+    assert geo.nb <= 32  # no row is split by itself
+    n, many = work_list_heads(out.shape[0] * out.shape[1] * geo.nb, *tensors)
+    for flags in (0, fva.FVA_SCHED_UNPAIRED):
+        assert torch.equal(attend(flags, *many), out.repeat(1, n, 1, 1))
+    return [attend(fva.FVA_SPLIT_BLOCKS(s), *tensors) for s in sorted({1, geo.nb // 2}) if 0 < s < geo.nb]
+
+
 @pytest.mark.parametrize("case", range(30))
 def test_random_small_config(case):
     fva, torch = lib(), torch_mod()
@@ -60,7 +76,7 @@ def test_random_small_config(case):
     O = out.float().cpu().numpy().astype(np.float64)
     assert np.array_equal(m.sum(axis=-1), c)
     band = tie = 0
-    errs = []
+    errs, refs = [], {}
     for b in range(cfg.batch):
         ref = route_ref(f64(Qb[b]), f64(Kb[b]), cfg.p, cfg.k_min, geo)
         cmp = compare_mask_rows(m[b].reshape(-1, nb), ref["mask"].reshape(-1, nb), ref["order"].reshape(-1, nb),
@@ -72,8 +88,14 @@ def test_random_small_config(case):
         for h in range(cfg.heads):
             for i in range(nb):
                 assert np.array_equal(kvn[b, h, i, : c[b, h, i]], np.nonzero(m[b, h, i])[0])
-            o_ref = attn_ref_head(f64(Qb[b, h]), f64(Kb[b, h]), f64(Vb[b, h]), m[b, h], geo)
-            errs.append(np.abs(O[b, h] - o_ref).ravel())
+            refs[b, h] = attn_ref_head(f64(Qb[b, h]), f64(Kb[b, h]), f64(Vb[b, h]), m[b, h], geo)
+            errs.append(np.abs(O[b, h] - refs[b, h]).ravel())
+    attend = lambda flags, q, k, v, *lists: fva.fva_attn(q, k, v, tiling, *lists, flags=flags)
+    for cut in over_the_work_list(attend, (q, k, v, mask, counts, kv), geo, out):
+        cut = cut.float().cpu().numpy().astype(np.float64)
+        for b in range(cfg.batch):
+            for h in range(cfg.heads):
+                errs.append(np.abs(cut[b, h] - refs[b, h]).ravel())
     e = np.concatenate(errs)
     log(f"[random {case}] grid {cfg.grid} tile {cfg.tile} batch {cfg.batch} heads {cfg.heads} p {cfg.p} "
         f"k_min {cfg.k_min}: nb {nb}, retained {c.mean() / nb:.3f}, band {band} tie {tie}, "
@@ -99,14 +121,18 @@ def test_random_small_config_fp8v(case):
     out = fva.fva_attn_fp8v(q, k, v8, vexp, tiling, mask, counts, kv)
     torch.cuda.synchronize()
     m = mask.cpu().numpy()
-    O = out.float().cpu().numpy().astype(np.float64)
+
+    attend = lambda flags, q, k, v8, e, *lists: fva.fva_attn_fp8v(q, k, v8, e, tiling, *lists, flags=flags)
     rows = {h: list(range(geo.nb)) for h in range(cfg.heads)}
-    for b in range(cfg.batch):
-        compare_rows(f"random {case} batch {b}", Qb[b:b + 1], Kb[b:b + 1], Vb[b:b + 1], m[b], O[b], geo, rows)
-        for h in range(cfg.heads):
-            for i in range(geo.nb):
-                if not m[b, h, i].any():
-                    assert np.all(O[b, h][geo.block_tokens[i]] == 0)
+    for n, o in enumerate([out] + over_the_work_list(attend, (q, k, v8, vexp, mask, counts, kv), geo, out)):
+        O = o.float().cpu().numpy().astype(np.float64)
+        for b in range(cfg.batch):
+            compare_rows(f"random {case} batch {b} run {n}", Qb[b:b + 1], Kb[b:b + 1], Vb[b:b + 1], m[b], O[b], geo,
+                         rows)
+            for h in range(cfg.heads):
+                for i in range(geo.nb):
+                    if not m[b, h, i].any():
+                        assert np.all(O[b, h][geo.block_tokens[i]] == 0)
 
 
 @pytest.mark.parametrize("case", range(30))

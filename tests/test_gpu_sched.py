@@ -6,7 +6,9 @@ the queue counters), every row must be run exactly once: with few enough kept
 blocks that no row is split, the persistent launch equals the naive grid bit
 for bit, and rows left out would keep the NaN that the output starts with.
 Short rows that all fit on the device take the naive grid by themselves; more
-than 32 blocks or more than 512 rows reach the work list.
+than 32 blocks or more than 512 rows reach the work list. Shapes that take the
+naive grid are compared with the same heads repeated until they no longer do:
+more rows, on the work list, each wave with two query tiles.
 """
 
 import numpy as np
@@ -14,7 +16,7 @@ import pytest
 
 from oracle.compare import ATTN_MAX_ABS
 
-from _gpu_util import custom_config, geometry_of, lib, tiling_of, to_dev, torch_mod
+from _gpu_util import custom_config, geometry_of, lib, tiling_of, to_dev, torch_mod, work_list_heads
 
 pytestmark = pytest.mark.gpu
 
@@ -44,10 +46,14 @@ def test_every_item_runs_once(heads, grid, tile):
     mask[np.cumsum(mask, -1) > 32] = 0  # the smallest automatic chunk: nothing is split
     m = torch.from_numpy(mask).cuda()
     want = fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=fva.FVA_SCHED_NAIVE)
-    for flags in (0, fva.FVA_SCHED_UNPAIRED):
-        out = torch.full_like(q, float("nan"))
-        fva.fva_attn(q, k, v, tiling_of(cfg), m, flags=flags, out=out)
-        assert torch.equal(out, want)
+    calls = [(1, (q, k, v, m))]
+    if geo.nb <= 32 and heads * geo.nb <= 512:
+        calls.append(work_list_heads(heads * geo.nb, q, k, v, m))
+    for n, (qn, kn, vn, mn) in calls:
+        for flags in (0, fva.FVA_SCHED_UNPAIRED):
+            out = torch.full_like(qn, float("nan"))
+            fva.fva_attn(qn, kn, vn, tiling_of(cfg), mn, flags=flags, out=out)
+            assert torch.equal(out, want.repeat(1, n, 1, 1))
 
 
 @pytest.mark.parametrize(

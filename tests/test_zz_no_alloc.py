@@ -1,8 +1,8 @@
 """GPU check of fva_attn_noalloc, the allocation-free attention call.
 
-The call runs fva_attn's persistent path on the library's static device
-scratch. Two calls in a row, the second on a smaller input (the scratch
-keeps the first call's contents), each compared with fva_attn on the same
+The call runs fva_attn on the library's static device scratch. Calls in a
+row, each on a smaller input (the scratch keeps the earlier calls' contents),
+each compared with fva_attn on the same
 inputs and lists: identical where fva_attn splits no row, and within the
 attention bar (max 2e-2, mean 1e-3 against the fp64 oracle) where its
 automatic chunk size splits rows that the allocation-free call keeps whole.
@@ -62,13 +62,21 @@ def test_noalloc_two_calls_second_smaller():
     log(f"[noalloc] 480p: identical to fva_attn; oracle rows max {emax:.3e} mean {emean:.3e}")
     assert emax <= ATTN_MAX_ABS and emean <= ATTN_MEAN_ABS
     del q, k, v, mask, counts, kv, O_ref, O_na
-    # call 2: the 2-head 3x16x16 case, on the scratch the first call left
+    # call 2: a smaller work list over the first one's, on the scratch it left:
+    # the 3x16x16 clip's two heads 43 times over, 1032 rows
     cfg2 = synth.get_config("tiny")
     Q2, K2, V2 = workload("tiny")
+    q, k, v, mask, counts, kv = routed(cfg2, *(np.tile(x, (1, 43, 1, 1)) for x in (Q2, K2, V2)))
+    O_ref = fva.fva_attn(q, k, v, tiling_of(cfg2), mask, counts, kv, flags=fva.FVA_SCHED_NAIVE)
+    O_na = noalloc(q, k, v, cfg2, counts, kv)
+    assert torch.equal(O_na, O_ref)
+    O_many = O_na
+    # call 3: the two heads alone, which take the plain grid
     q, k, v, mask, counts, kv = routed(cfg2, Q2, K2, V2)
     O_ref = fva.fva_attn(q, k, v, tiling_of(cfg2), mask, counts, kv)
     O_na = noalloc(q, k, v, cfg2, counts, kv)
     assert torch.equal(O_na, O_ref)
+    assert torch.equal(O_na.repeat(1, 43, 1, 1), O_many)
     emax, emean = oracle_errors(cfg2, Q2, K2, V2, mask.cpu().numpy(), O_na.float().cpu().numpy(), [0, 1],
                                 range(12))
     log(f"[noalloc] tiny after 480p: identical to fva_attn; every element max {emax:.3e} mean {emean:.3e}")
