@@ -88,9 +88,9 @@ typedef struct fva_qkv_desc {
 /* Persistent scheduler only: run every query block as an item of its own.
  * Without it, two neighbouring query blocks that both hold at most 64 real
  * tokens and are both unsplit run (where the items left still fill the
- * device) as one 128-row item over the union of their kept lists (each block on two of the four waves, each wave skipping
- * the key blocks its block does not keep), so that every K/V tile either
- * keeps is staged once. Neighbours are x-neighbours (ix, ix + 1), ix even,
+ * device) as one 128-row item over the union of their kept lists (each block
+ * on two of the four waves, each wave skipping the key blocks its block does
+ * not keep), so that every K/V tile either keeps is staged once. Neighbours are x-neighbours (ix, ix + 1), ix even,
  * of one (t, y) line; among the blocks no such pair holds, y-neighbours
  * (iy, iy + 1), iy even, of one (t, x) column. Each row still sees exactly
  * its own key blocks in ascending order: the output is the same bit for
@@ -357,7 +357,8 @@ fva_status fva_attn_fp8v(const void* Q, const void* K, const uint8_t* V8, const 
 /*
  * Allocation-free attention, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): fva_attn with the persistent scheduler, whose work list, plan
+ * hipMalloc): fva_attn with the persistent scheduler (calls whose rows all fit
+ * on the device at once run as the naive grid), whose work list, plan
  * scratch and block records live in a static device array of the library
  * (16 MiB on every device the library runs on, held until the process
  * ends) instead of a caller workspace. The call allocates nothing.
@@ -373,7 +374,7 @@ fva_status fva_attn_fp8v(const void* Q, const void* K, const uint8_t* V8, const 
  * identical. Inputs, O, trace and errors as for fva_attn.
  *
  * A shape needs, of the 16 MiB, the queue items (4 bytes per query block),
- * two per-row prefixes (8 bytes per query block + 8), 76 bytes per head,
+ * 8 bytes per query block + 8 reserved for the plan, 76 bytes per head,
  * 32 bytes per block of the tiling and 80 bytes of queue bookkeeping, each
  * part rounded up to 256 bytes: with nb = 660 about 2,000 heads fit. A
  * shape needing more returns FVA_ERR_SCRATCH before anything is launched.

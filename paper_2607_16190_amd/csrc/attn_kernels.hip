@@ -767,7 +767,7 @@ __device__ void process_item(const AttnParams& P, int row, int begin, int end, f
     for (int c = 0; c < cnt; ++c) {
       const int nj = mc.n;
       const int ng = ngroups_of(nj);
-      // K_c landed (the four copies of V8_c, issued after it, may be in flight).
+      // K_c landed (the 16 / NW copies of V8_c, issued after it, may be in flight).
       wait_vmem<16 / NW>();
       tile_barrier();
       const bool act = active && !(fq & hbit);
@@ -1201,8 +1201,10 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // for the plan. All of it is latency: loads that do not depend on one another
 // are issued together, and the plan's passes (four, with a barrier between)
 // exchange only per-head values, in LDS. As three launches, with the plan's
-// values in memory: 18 us for 2 heads of 12 blocks, 44 us for 5 of 308 and 71
-// us for 40 of 660; this way 6, 22 and 53 us.
+// values in memory: 18 us for 2 heads of 12 blocks, 44 us for 5 of 308, 71 us
+// for 40 of 660, 55 us for 16 of 960 and 380 us for 600 of 128; this way 6, 22,
+// 48, 48 and 198 us. (The instances for more than 512 blocks spill 15 to 56
+// registers of a lane's counts, outside the passes' inner loops.)
 //
 // Chunks (the split part of the scheduler): with S = `forced` (> 0) or, by
 // default, S = max(kMinChunk, ceil(total / (2 * slots))), total being the sum
@@ -1228,9 +1230,15 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // classes of decreasing cost instead, in the order above within a class: with so
 // few items per slot the launch ends when the last long one does. 5 heads of
 // 480p (1540 rows, 257 of them cut in two): 87 % of the slots' time was busy
-// before, 90 % in classes; 1534 -> 1483 us. With more rows there is nothing to
-// gain and the heads' order keeps more of K/V in the caches: 40 heads of 480p
-// (12320 rows) 10534 us, 10642 in classes.
+// before, 90 % in classes; 1502 -> 1402 us. What the classes give falls with the
+// number of rows and grows with their length; fva_attn in the heads' order and
+// in classes, us: 960 rows of 960 blocks 4866, 4212; 924 of 308 955, 875; 640 of
+// 128 369, 352; 2640 of 660 5992, 5994; 5760 of 960 19966, 19552; 7920 of 660
+// 17208, 17033. Rows of at most 308 blocks lose a little from 2000 rows on
+// (4928 of 308 4322, 4335; 8008 of 308 6976, 6996; 7680 of 128 3393, 3397), and
+// with about three rows a slot either order can end badly (1280 of 64 333, 350;
+// 1440 of 480 2576, 2630). Above, the heads' order keeps more of K/V in the
+// caches: 40 heads of 480p (12320 rows) 10534 us, 10642 in classes.
 //
 // Scratch: per head cost, rank, run starts [kQueues], items before each run
 // [kQueues + 1], first chunk and first split record; in LDS up to
@@ -1665,7 +1673,8 @@ struct AttnWorkspace {
   int32_t* qbase;    // [kQueues + 1]
   int32_t* qctr;     // [kQueues]
   int32_t* hscratch; // [heads * (2 + 2 * kQueues + 1)]
-  int32_t* rscratch; // [2 * (rows + 1)] per-row prefixes
+  int32_t* rscratch; // [2 * (rows + 1)], of which the plan uses 2 per head from kPlanLdsHeads
+                     // heads on (the sizes that the queries return stay as they are)
   int32_t* n_split;  // [1]
   int4* chunks;      // [cap]
   int4* splits;      // [cap]
@@ -1862,9 +1871,13 @@ hipError_t launch_attn(const AttnArgs& a) {
   P.pairs_head = pairs ? ws.pairs_head : 0;
 
   // The naive grid runs the same item body: also for calls whose rows all fit
-  // on the device at once and are too short to be split (no kept list exceeds
-  // the smallest chunk), where the work list would only be waited for: 2 heads
-  // of 12 blocks 19 us instead of 25, 40 heads (480 rows) 29 instead of 54.
+  // on the device at once and are not split (no kept list exceeds the smallest
+  // chunk, or the call is the allocation-free one, which splits none), where the
+  // work list would only be waited for: 2 heads of 12 blocks 19 us instead of 25,
+  // 40 heads (480 rows) 29 instead of 54. Long rows, allocation-free: 128 of 128
+  // blocks 170 instead of 195, 308 of 308 477 instead of 502, 500 of 250 493
+  // instead of 511, 480 of 480 1032 instead of 1059, 512 of 512 1164 instead of
+  // 1189: the work list's order gains nothing where every row starts at once.
   const int forced = (int)((a.flags >> 8) & 0xFFFFu);
   const bool whole = a.lean || g.nb <= (forced > 0 ? forced : kMinChunk);
   if ((a.flags & 1u) || (whole && n_items <= slots)) {

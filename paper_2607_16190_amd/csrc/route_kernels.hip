@@ -855,9 +855,12 @@ hipError_t launch_route(const RouteArgs& a) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // Key parts per (head, query tile): up to four workgroups per CU of a 256-CU
-  // device (what its registers hold), at least one key tile per wave. Score
-  // kernel of 5 heads of 480p (100 pairs) 15.5 us in one part, 6.5 us in five; 5
-  // heads of 720p (210 pairs) 30 us, 18 us in four; from 513 pairs on one part.
+  // device (what its registers hold), at least one key tile per workgroup (the
+  // last part's other waves may have none). Score kernel of 5 heads of 480p (100
+  // pairs) 15.5 us in one part, 6.5 us in five; 5 heads of 720p (210 pairs) 30 us,
+  // 18 us in four. fva_route: 12 heads of 720p (504 pairs) 147.6 us in one part,
+  // 141.5 in two; 24 heads of 480p (480 pairs) 119.4, 118.6. From 513 pairs on one
+  // part: two would be more workgroups than the device holds at once.
   const int score_pairs = (g.nb + kSelRows - 1) / kSelRows * bhs;
   const int key_tiles = padded_blocks(g.nb) / 16;
   const int parts = std::max(1, std::min(1024 / score_pairs, (key_tiles + 3) / 4));
