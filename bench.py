@@ -230,23 +230,23 @@ def cpu_baseline(cfg, Qb, Kb, Vb, mask, counts, budget_s=20.0, blocks="box"):
 # counter reads for a device copy of known size; valid only for the attention
 # source with this digest (null otherwise).
 ATTN_TRAFFIC = {
-    "source_digest": "2f3037edb6dfe87c",
+    "source_digest": "60f6be703520d76d",
     "bytes": {
-        "720p": ((106332992 + 107636997) // 2 * 2 + 757000) * 1024,
-        "720p-hilbert": ((78494147 + 78194246) // 2 * 2 + 757152) * 1024,
-        "720p-fp8v": ((70670733 + 70880901) // 2 * 2 + 759442) * 1024,
-        "720p-hilbert-fp8v": ((66930490 + 66836343) // 2 * 2 + 759372) * 1024,
+        "720p": ((103927717 + 104172808) // 2 * 2 + 757026) * 1024,
+        "720p-hilbert": ((79158314 + 78542691) // 2 * 2 + 757166) * 1024,
+        "720p-fp8v": ((71189722 + 71277918) // 2 * 2 + 759467) * 1024,
+        "720p-hilbert-fp8v": ((67021487 + 66965307) // 2 * 2 + 759400) * 1024,
     },
 }
 # Same for fva_route (pool_kernel + score_kernel + select_kernel), per call
 # (FETCH x 2, WRITE x 1, KiB per dispatch summed over the three kernels).
 ROUTE_TRAFFIC = {
-    "source_digest": "2424d22d3bd8d3a4",
+    "source_digest": "e36a670f51a13ee9",
     "bytes": {
-        "720p": ((756153 + 29370 + 68497) * 2 + 53760 + 142321 + 49285) * 1024,
-        "720p-hilbert": ((756145 + 25392 + 55237) * 2 + 47360 + 116771 + 39989) * 1024,
-        "720p-fp8v": ((756161 + 29400 + 68482) * 2 + 53760 + 142149 + 49285) * 1024,
-        "720p-hilbert-fp8v": ((756141 + 25391 + 55238) * 2 + 47360 + 116890 + 39989) * 1024,
+        "720p": ((756154 + 29331 + 68493) * 2 + 53760 + 142141 + 49285) * 1024,
+        "720p-hilbert": ((756142 + 25417 + 55228) * 2 + 47360 + 116852 + 39989) * 1024,
+        "720p-fp8v": ((756162 + 29393 + 68474) * 2 + 53760 + 142125 + 49285) * 1024,
+        "720p-hilbert-fp8v": ((756153 + 25396 + 55240) * 2 + 47360 + 117013 + 39989) * 1024,
     },
 }
 
