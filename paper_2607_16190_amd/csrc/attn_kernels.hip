@@ -307,6 +307,19 @@ __device__ __forceinline__ float row_max4(float v) {
 // wave waits for its own copies (vmcnt) before arriving here.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// s * c2 + negm, the argument of a score's exponential, in the score's own
+// register. Left to itself the compiler may give all arguments one temporary (it
+// does, with one more free register than it needs), and then each waits for the
+// exponential of the one before: the two no longer run side by side and half of
+// the PV phase's exponentials come a product later. 59 heads of 325 full blocks
+// 36.8 -> 36.4 ms, 40 heads of 720p with random lists 54.7 -> 54.3, 48 heads of
+// 20x31x42 14.70 -> 14.57. (The scores' products are complete here: their maximum
+// has been taken, and negm depends on it.)
+__device__ __forceinline__ float exp2_arg(float s, float c2, float negm) {
+  asm("v_fma_f32 %0, %1, %0, %2" : "+v"(s) : "s"(c2), "v"(negm));
+  return s;
+}
+
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // S^T tiles of one 64-key half: LDS tiles 4hb .. 4hb + 2*NGH - 1 against the
@@ -588,7 +601,7 @@ __device__ void process_item(const AttnParams& P, int row, int begin, int end, f
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) s[t][nt][r] = __builtin_amdgcn_exp2f(fmaf(s[t][nt][r], P.c2, negm[nt]));
+        for (int nt = 0; nt < NT; ++nt) s[t][nt][r] = __builtin_amdgcn_exp2f(exp2_arg(s[t][nt][r], P.c2, negm[nt]));
       }
     }
 #pragma unroll
@@ -624,7 +637,7 @@ __device__ void process_item(const AttnParams& P, int row, int begin, int end, f
         if (!short_half) {
           constexpr int t = 2 + (u >> 2), r = u & 3;
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) s[t][nt][r] = __builtin_amdgcn_exp2f(fmaf(s[t][nt][r], P.c2, negm[nt]));
+          for (int nt = 0; nt < NT; ++nt) s[t][nt][r] = __builtin_amdgcn_exp2f(exp2_arg(s[t][nt][r], P.c2, negm[nt]));
         }
         if constexpr (u == 7) {
           if (!short_half) {
@@ -824,10 +837,11 @@ __device__ void process_item(const AttnParams& P, int row, int begin, int end, f
   // The loop's first instruction lies 16 bytes past a 32-byte boundary (three
   // nops and the four bytes more that the moves between them and the loop take):
   // its time depends on where its products fall in the 32-byte instruction
-  // fetches. Over the eight placements 4 bytes apart, 16 heads of a 111,600-token
-  // clip took 17.60 (16 and 20 bytes past) to 17.84 ms (12 past), 16 heads of 720p
-  // 23.19 to 23.43. Without this line the code before the loop decides, and a
-  // change there cost 0.2 to 1 % of every large call.
+  // fetches. Over the eight placements 4 bytes apart, 59 heads of 325 full blocks
+  // took 36.3 (8 past), 36.5 (16) to 36.9 ms (12 and 20), 49 heads of 6x43x84 in
+  // 64-token blocks 13.51 (16) to 13.66 (28), 40 heads of 720p 51.9 (8), 52.1 (16)
+  // to 52.3 (28); 16 is the one that none of the six shapes tried loses much at.
+  // Without this line the code before the loop decides.
   asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
   for (int c = 0; c < cnt; ++c) {
     const int nj = mc.n;
