@@ -1254,6 +1254,16 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // 1440 of 480 2576, 2630). Above, the heads' order keeps more of K/V in the
 // caches: 40 heads of 480p (12320 rows) 10534 us, 10642 in classes.
 //
+// Where no row is split (the allocation-free call) a pair's class is that of a
+// quarter more than its cost: its union is longer than its longer list, and
+// nothing else in the call is as long, so a pair that starts late is what the
+// launch waits for. fva_attn_noalloc on routed lists without the quarter, with it,
+// and (in brackets) without pairs: 2 heads of 480p 968, 885 (893) us, 4 heads 1004,
+// 927 (928), 5 heads 1345, 1280 (1286); 8 heads of 16x26x43 700, 672 (724); 5 heads
+// of 720p 6550, 6496 (6609). (Lists that neighbours
+// do not share are up to a quarter faster without pairs, but counts do not tell.)
+// Split calls keep the plain cost: 5 heads of 480p 0.99x to 1.05x, 3 heads 0.98x.
+//
 // Scratch: per head cost, rank, run starts [kQueues], items before each run
 // [kQueues + 1], first chunk and first split record; in LDS up to
 // kPlanLdsHeads heads, else in hscratch and (the last two) rscratch. R: rounds
@@ -1300,6 +1310,7 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
   int* hsplit = hchunk + n_heads;
 
   const bool sorted = IN_LDS && n_heads <= kSortHeads && n_heads * nb <= kSortRows;
+  const bool unsplit = chunk_cap == 0;
   int S = 0;  // chunk size
 
   // a lane's rows of head h: i = 64k + lane, all loads in flight at once
@@ -1400,6 +1411,7 @@ __global__ __launch_bounds__(kPlanThreads) void prep_kernel(
             if (sorted) {
               // class of one of the row's items, the highest cost first
               int w = cn[k];
+              if (unsplit && poffs[i] > 0) w += w / 4;
               if (c[k] > 1) w = (w + c[k] - 1) / c[k];
               const int cl = kClasses - 1 - min((int)((float)w * class_scale), kClasses - 1);
               atomicAdd(&cls[(h * kQueues + run) * kClasses + cl], c[k]);

@@ -18,6 +18,7 @@ from oracle import attn_ref_rows
 from oracle.compare import ATTN_MAX_ABS, ATTN_MEAN_ABS
 
 from _gpu_util import custom_config, f64, geometry_of, lib, log, tiling_of, to_dev, torch_mod, workload
+from test_gpu_pairs import pairs_of
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +146,37 @@ def test_noalloc_graph_holds_two_launches():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, noalloc(q, k, v, cfg, counts, kv))
+
+
+@pytest.mark.parametrize("heads, grid, tile", [(2, (21, 30, 52), (2, 8, 8)), (4, (16, 26, 43), (2, 8, 8))])
+def test_noalloc_pairs_start_first(heads, grid, tile):
+    """No row is split here, so a query-block pair is the longest item there is: with all rows
+    equally long, and more of them than workgroups, every pair starts before any item ends (the
+    items that begin later are single rows)."""
+    torch, fva = torch_mod(), lib()
+    cfg = custom_config("pairs_first", heads, grid, tile, [1.0] * heads, 5)
+    geo, t = geometry_of(cfg), tiling_of(cfg)
+    nb, kept = geo.nb, geo.nb // 2
+    pairs = pairs_of(geo)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert pairs and 2 * len(pairs) < nb  # (a tiling with pairs at its edges only)
+    assert 2 * cus < heads * (nb - len(pairs))  # pairs are formed, and some items have to wait
+    g = torch.Generator(device="cuda:0").manual_seed(11)
+    N = geo.block_sizes.sum()
+    q, k, v = (torch.randn(1, heads, int(N), 128, generator=g, device="cuda:0").bfloat16() for _ in range(3))
+    counts = torch.full((1, heads, nb), kept, dtype=torch.int32, device="cuda:0")
+    kv = torch.zeros((1, heads, nb, nb), dtype=torch.int32, device="cuda:0")
+    kv[..., :kept] = torch.arange(kept, dtype=torch.int32, device="cuda:0")
+    desc = fva._desc_of(q)
+    trace = torch.zeros(fva.fva_trace_words(desc, t), dtype=torch.int64, device="cuda:0")
+    for _ in range(2):  # (the first launch of a process starts its workgroups later)
+        out = torch.full_like(q, float("nan"))
+        fva.fva_attn_noalloc(q, k, v, t, counts, kv, out, flags=fva.FVA_TRACE, trace=trace)
+        torch.cuda.synchronize()
+    tr = trace.view(-1, 4)[: heads * nb].cpu().numpy()
+    first = np.zeros(nb, bool)
+    first[[a for a, _ in pairs]] = True
+    second = np.zeros(nb, bool)
+    second[[b for _, b in pairs]] = True
+    start, end = tr[:, 0].reshape(heads, nb), tr[:, 1].reshape(heads, nb)
+    assert (start[:, first] < end[:, ~first & ~second].min()).all()
