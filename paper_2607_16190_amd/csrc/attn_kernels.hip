@@ -1133,7 +1133,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_persistent_kernel(AttnPa
 constexpr int kMinChunk = 32;        // smallest automatic chunk (kept blocks)
 constexpr int kPlanThreads = 1024;   // one thread per block of the tiling
 constexpr int kPlanLdsHeads = 1024;  // heads whose bookkeeping the plan keeps in LDS
-constexpr int kSortHeads = 64;       // heads and rows up to which a queue's items are put in
+constexpr int kSortHeads = 20;       // heads and rows up to which a queue's items are put in
 constexpr int kSortRows = 8192;      // order of cost, in kClasses classes
 constexpr int kClasses = 16;
 static_assert(kMaxBlocks <= kPlanThreads, "one thread per block");
@@ -1240,19 +1240,19 @@ __device__ __forceinline__ int pair_union(const int32_t* __restrict__ counts, co
 // same head at the same time (its K/V stay in the shared last-level cache)
 // and the resident workgroups of one XCD work on neighbouring query blocks
 // (their kept K/V blocks overlap in L2).
-// Calls of up to kSortRows rows (16 per workgroup slot) run a queue's items in
-// classes of decreasing cost instead, in the order above within a class: with so
-// few items per slot the launch ends when the last long one does. 5 heads of
-// 480p (1540 rows, 257 of them cut in two): 87 % of the slots' time was busy
-// before, 90 % in classes; 1502 -> 1402 us. What the classes give falls with the
-// number of rows and grows with their length; fva_attn in the heads' order and
-// in classes, us: 960 rows of 960 blocks 4866, 4212; 924 of 308 955, 875; 640 of
-// 128 369, 352; 2640 of 660 5992, 5994; 5760 of 960 19966, 19552; 7920 of 660
-// 17208, 17033. Rows of at most 308 blocks lose a little from 2000 rows on
-// (4928 of 308 4322, 4335; 8008 of 308 6976, 6996; 7680 of 128 3393, 3397), and
-// with about three rows a slot either order can end badly (1280 of 64 333, 350;
-// 1440 of 480 2576, 2630). Above, the heads' order keeps more of K/V in the
-// caches: 40 heads of 480p (12320 rows) 10534 us, 10642 in classes.
+// Calls of up to kSortRows rows (16 per workgroup slot) and kSortHeads heads run a
+// queue's items in classes of decreasing cost instead, in the order above within a
+// class: with so few items per slot the launch ends when the last long one does. 5
+// heads of 480p (1540 rows, 257 of them cut in two): 87 % of the slots' time was
+// busy before, 90 % in classes; 1502 -> 1402 us. What the classes give grows with
+// the rows' length and falls with their number; fva_attn on uneven rows, in the
+// heads' order / in classes: 1320 rows of 660 blocks 1.16, 3300 of 660 1.06, 7920 of
+// 660 1.02, 7680 of 960 1.03, 1540 of 308 1.09, 3696 of 308 1.06, 2000 of 200 1.08, 1280
+// of 128 1.05; on even rows 0.99 to 1.00 of 200 blocks and more. What they cost grows
+// with the number of heads, as those whose K and V are in use at a time fill the
+// caches: 17 heads of 308 blocks 1.01, 24 heads of 480p 0.98; 20 heads of 128
+// blocks 1.03, 41 heads 0.99, 61 heads 0.96; 20 heads of 64 blocks 1.02, 25 heads
+// 0.98; 59 heads of 6x43x45 0.96, 27 heads of 77 blocks 0.94 to 0.96.
 //
 // Where no row is split (the allocation-free call) a pair's class is that of a
 // quarter more than its cost: its union is longer than its longer list, and

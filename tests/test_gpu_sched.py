@@ -135,3 +135,28 @@ def test_noalloc_pairs_where_they_fit(heads):
     out = torch.full_like(q, float("nan"))
     fva.fva_attn_noalloc(q, k, v, tiling_of(cfg), counts, kv, out)
     assert torch.equal(out, fva.fva_attn(q, k, v, tiling_of(cfg), mask, counts, kv))
+
+
+@pytest.mark.parametrize("heads", [20, 21])
+def test_item_order_by_heads(heads):
+    """Up to 20 heads the long rows of all heads start before the short ones of any; with more
+    the heads run one after the other (in the order of their cost, here of their number)."""
+    torch, fva = torch_mod(), lib()
+    nb, long, short = 128, 32, 8  # (32: the smallest automatic chunk, so nothing is split)
+    t = fva.Tiling.curve(nb * 128, 128)
+    g = torch.Generator(device="cuda:0").manual_seed(91)
+    q, k, v = (torch.randn(1, heads, nb * 128, 128, generator=g, device="cuda:0").bfloat16() for _ in range(3))
+    is_long = torch.arange(nb, device="cuda:0") % 2 == 0
+    counts = torch.where(is_long, long, short).int().expand(1, heads, nb).contiguous()
+    ids = torch.arange(nb, dtype=torch.int32, device="cuda:0")
+    kv = ids.expand(1, heads, nb, nb).contiguous()
+    mask = (ids < counts[..., None]).to(torch.uint8)
+    trace = torch.zeros(fva.fva_trace_words(fva._desc_of(q), t), dtype=torch.int64, device="cuda:0")
+    out = fva.fva_attn(q, k, v, t, mask, counts, kv, flags=fva.FVA_TRACE, trace=trace)
+    want = fva.fva_attn(q, k, v, t, mask, counts, kv, flags=fva.FVA_SCHED_NAIVE)
+    assert torch.equal(out, want)
+    start = trace.view(-1, 4)[: heads * nb, 0].cpu().numpy().reshape(heads, nb)
+    assert (start > 0).all()
+    is_long = is_long.cpu().numpy()
+    first_short, last_long = np.median(start[0, ~is_long]), np.median(start[-1, is_long])
+    assert (first_short > last_long) if heads <= 20 else (first_short < last_long)
