@@ -230,12 +230,12 @@ def cpu_baseline(cfg, Qb, Kb, Vb, mask, counts, budget_s=20.0, blocks="box"):
 # counter reads for a device copy of known size; valid only for the attention
 # source with this digest (null otherwise).
 ATTN_TRAFFIC = {
-    "source_digest": "60f6be703520d76d",
+    "source_digest": "13a3804458455ad9",
     "bytes": {
-        "720p": ((103927717 + 104172808) // 2 * 2 + 757026) * 1024,
-        "720p-hilbert": ((79158314 + 78542691) // 2 * 2 + 757166) * 1024,
-        "720p-fp8v": ((71189722 + 71277918) // 2 * 2 + 759467) * 1024,
-        "720p-hilbert-fp8v": ((67021487 + 66965307) // 2 * 2 + 759400) * 1024,
+        "720p": ((108868825 + 111786055) // 2 * 2 + 756986) * 1024,
+        "720p-hilbert": ((77511450 + 77480517) // 2 * 2 + 757083) * 1024,
+        "720p-fp8v": ((70884610 + 70814703) // 2 * 2 + 759451) * 1024,
+        "720p-hilbert-fp8v": ((67010247 + 67138107) // 2 * 2 + 759394) * 1024,
     },
 }
 # Same for fva_route (pool_kernel + score_kernel + select_kernel), per call
